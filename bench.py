@@ -30,7 +30,7 @@ PEAK = {"bf16": 2500.0, "f32": 157.3}        # dense MFMA TFLOP/s, MI355X
 PREDICT_CHUNK = 2048                          # test rows per prediction launch (the library's chunk)
 HBM_PEAK_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_2310_10211_amd", "csrc")
-KERNEL_SOURCES = ["gevo_device.h", "gevo_internal.h", "gevo_kernels.hip", "gevo_fused.hip", "gevo_stream.hip",
+KERNEL_SOURCES = ["gevo_device.h", "gevo_internal.h", "gevo_kernels.hip", "gevo_tiles.hip", "gevo_fused.hip", "gevo_stream.hip",
                   "gevo_bwd.hip", "gevo_gemm.hip", "gevo_predict.hip"]
 # rocprofv3 kernel-name stem -> kernel kind of gevo_pop_kernel_stats (training kind, predict kind)
 KERNEL_KIND_OF = {"k_fused2": ("fused_train", None), "k_stream_layer": ("layer_train", "layer_fwd"),
@@ -38,7 +38,9 @@ KERNEL_KIND_OF = {"k_fused2": ("fused_train", None), "k_stream_layer": ("layer_t
                   "k_out_upd": ("out_train", None), "k_out": (None, "out_predict"),
                   "k_bwd_gemm": ("bwd", None), "k_bwd": ("bwd", None), "k_pred_gemm<true>": (None, "fwd_out"),
                   "k_pred_gemm<false>": (None, "layer_fwd"), "k_wt_bf16": (None, "weight_copy"),
-                  "k_fwd_gemm": (None, "layer_fwd")}
+                  "k_fwd_gemm": (None, "layer_fwd"), "k_tile_layer": ("layer_train", None),
+                  "k_tile_out": ("out_train", None), "k_tile_bwd": ("bwd", None), "k_tile_fwd": (None, "layer_fwd"),
+                  "k_tile_pred_out": (None, "out_predict")}
 
 
 def fused_workload(cfg):

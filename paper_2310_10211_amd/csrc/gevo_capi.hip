@@ -42,6 +42,7 @@ struct Layout {
   int L = 0, P = 0, B = 0, Bp = 0, T = 0;
   bool fused = false;                              // two-layer bf16 nets train in the fused per-variant kernel
   bool resident = false;                           // ... or, for the shapes it covers, in the resident kernel
+  bool tiles = false;                              // hidden layers and their data on tile-image operands
   bool images = false;                             // some layer trains on a register-image copy of its master
   int64_t n_train = 0, n_test = 0;
   int n_test_pad = 0, n_chunks_test = 0;
@@ -126,6 +127,11 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
   }
   if (out_lds(y.lay[y.L - 1].Kp, y.Bp, y.elt, pad) > kLdsBudget) return GEVO_E_UNSUPPORTED;
   y.fused = y.L == 2 && c->dtype == GEVO_BF16 && fused2_lds_bytes(y.lay[0].Np, y.Bp) > 0;
+  // Full-precision nets with a hidden layer run on the tile-image kernels in
+  // training and prediction at every size (one epoch and a prediction of 64
+  // variants of 784-256-10: 78 ms with row-major operands, 46 ms; 4 variants
+  // of 784-128-10 on 2,048 rows: 5.0 and 2.7 ms).
+  y.tiles = y.L > 1 && c->dtype == GEVO_F32;
   y.resident = y.fused && res2_supported(y.lay[0].Kp, y.lay[0].Np, y.Bp, (int)c->dims[2]) && resident_requested();
   for (int l = 0; l + 1 < y.L; ++l) {
     LayerLay& q = y.lay[l];
@@ -154,7 +160,7 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
     q.ident = take(P * 4);
     q.base_w = take(Np * Kp * 4);
     q.base_b = take(Np * 4);
-    if (l >= 1 && l < y.L - 1) q.Wt = take(P * Kp * Np * e);         // hidden layer >= 2
+    if (l >= 1 && l < y.L - 1 && !y.tiles) q.Wt = take(P * Kp * Np * e);         // hidden layer >= 2
     if (l < y.L - 1) {                                                // hidden layer: activations
       for (int bsel = 0; bsel < 2; ++bsel) {
         q.arows[bsel] = take(P * Bp * Np * e);
@@ -349,8 +355,8 @@ LaunchEv prof(gevo_pop* p, int kind) {
 // forward of hidden layer l over the R rows of a training batch (layer 0
 // reads arows0; deeper layers the previous layer's activations of buffer
 // outsel), writing the activations of buffer outsel in both orientations
-template <typename S>
-gevo_status forward_layer(gevo_pop* p, int l, const S* arows0, size_t ar0_vs, int R, int outsel) {
+gevo_status forward_layer(gevo_pop* p, int l, const uint16_t* arows0, size_t ar0_vs, int R, int outsel) {
+  typedef uint16_t S;
   const Layout& y = p->y;
   const LayerLay& q = y.lay[l];
   LayerArgs<S> a{};
@@ -368,25 +374,106 @@ gevo_status forward_layer(gevo_pop* p, int l, const S* arows0, size_t ar0_vs, in
   a.vtime = at<unsigned long long>(p, y.vtime);
   if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
   if (a.Kp % kTile || a.Np % kTile || a.R % kTile || a.R <= 0) return GEVO_E_SHAPE;
-  if constexpr (std::is_same<S, uint16_t>::value) {
-    if (q.streamed) {
-      a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
-      HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
-      return GEVO_OK;
-    }
+  if (q.streamed) {
+    a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
+    HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
+    return GEVO_OK;
   }
   HIP_TRY(launch_layer<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
   return GEVO_OK;
 }
 
-template <typename S>
-gevo_status forward_hidden(gevo_pop* p, const S* arows0, size_t ar0_vs, int R, int outsel) {
+gevo_status forward_hidden(gevo_pop* p, const uint16_t* arows0, size_t ar0_vs, int R, int outsel) {
   for (int l = 0; l < p->y.L - 1; ++l) {
-    gevo_status st = forward_layer<S>(p, l, arows0, ar0_vs, R, outsel);
+    gevo_status st = forward_layer(p, l, arows0, ar0_vs, R, outsel);
     if (st != GEVO_OK) return st;
   }
   return GEVO_OK;
 }
+
+// Tile-image nets: layer l of step t (update from the step's gradient, unless
+// t < 0) and the forward of step t + 1 (unless it is the epoch's last).  The
+// last hidden layer's launch also updates the output layer and the totals.
+template <typename S>
+gevo_status tile_layer(gevo_pop* p, int l, int t) {
+  const Layout& y = p->y;
+  const LayerLay& q = y.lay[l];
+  const bool upd = t >= 0, fwd = t + 1 < y.T;
+  const int buf = t & 1, nb = buf ^ 1;             // activations of step t and t + 1
+  const size_t xstep = (size_t)y.Bp * y.lay[0].Kp;
+  TileLayerArgs<S> a{};
+  a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
+  a.Wm = at<float>(p, q.Wm); a.bias = at<float>(p, q.bias); a.mask = at<uint32_t>(p, q.mask);
+  a.bmask = at<uint32_t>(p, q.bmask);
+  a.lr = at<float>(p, y.lrh) + (size_t)l * y.P;    // 0 for the variants that removed this layer
+  if (upd) {
+    a.G = at<S>(p, q.gcols);
+    if (l == 0) a.Acols = at<S>(p, y.xcols) + (size_t)t * xstep;
+    else { a.Acols = at<S>(p, y.lay[l - 1].acols[buf]); a.ac_vs = (size_t)y.lay[l - 1].Np * y.Bp; }
+    if (l == y.L - 2) {
+      const LayerLay& o = y.lay[y.L - 1];
+      a.WL = at<float>(p, o.Wm); a.biasL = at<float>(p, o.bias);
+      a.maskL = at<uint32_t>(p, o.mask); a.bmaskL = at<uint32_t>(p, o.bmask); a.lrL = at<float>(p, y.lr);
+      a.Hcols = at<S>(p, q.acols[buf]);
+      a.GL = at<S>(p, y.ogrd);
+      a.opdb = at<float>(p, y.opdb); a.opce = at<double>(p, y.opce); a.opcorr = at<unsigned int>(p, y.opcorr);
+      a.ce_acc = at<double>(p, y.train_ce); a.correct_acc = at<unsigned long long>(p, y.train_corr);
+    }
+  }
+  if (fwd) {
+    if (l == 0) a.Xrows = at<S>(p, y.xrows) + (size_t)(t + 1) * xstep;
+    else { a.Xrows = at<S>(p, y.lay[l - 1].arows[nb]); a.xr_vs = (size_t)y.Bp * y.lay[l - 1].Np; }
+    a.Orows = at<S>(p, q.arows[nb]); a.Ocols = at<S>(p, q.acols[nb]);
+  }
+  a.vtime = at<unsigned long long>(p, y.vtime);
+  if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
+  HIP_TRY(launch_tile_layer<S>(a, y.P, upd, fwd, p->stream,
+                               prof(p, upd ? GEVO_KERNEL_LAYER_TRAIN : GEVO_KERNEL_LAYER_FWD)));
+  return GEVO_OK;
+}
+
+// One SGD step of a tile-image net.
+template <typename S>
+gevo_status tile_step(gevo_pop* p, int t) {
+  const Layout& y = p->y;
+  const int L = y.L, buf = t & 1;
+  const int64_t r0 = (int64_t)t * y.B;
+  const int bt = (int)((y.n_train - r0) < y.B ? (y.n_train - r0) : y.B);
+  {
+    const LayerLay& o = y.lay[L - 1];
+    const LayerLay& h = y.lay[L - 2];
+    TileOutArgs<S> a{};
+    a.Kp = o.Kp; a.C = o.N; a.Bp = y.Bp;
+    a.WL = at<float>(p, o.Wm); a.bias = at<float>(p, o.bias);
+    a.Arows = at<S>(p, h.arows[buf]); a.Acols = at<S>(p, h.acols[buf]);
+    a.labels = at<int32_t>(p, y.yep) + (size_t)t * y.Bp;
+    a.scale = (float)(1.0 / (double)bt);
+    a.gscale = p->gscale_on ? at<float>(p, y.gscale) : nullptr;
+    a.Gcols = at<S>(p, h.gcols);
+    if (h.grows) a.Grows = at<S>(p, h.grows);
+    a.GL = at<S>(p, y.ogrd);
+    a.opdb = at<float>(p, y.opdb); a.opce = at<double>(p, y.opce); a.opcorr = at<unsigned int>(p, y.opcorr);
+    a.vtime = at<unsigned long long>(p, y.vtime);
+    HIP_TRY(launch_tile_out<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_OUT_TRAIN)));
+  }
+  for (int l = L - 2; l >= 1; --l) {               // pre-update weights, top down
+    const LayerLay& q = y.lay[l];
+    const LayerLay& h = y.lay[l - 1];
+    TileBwdArgs<S> a{};
+    a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
+    a.Wm = at<float>(p, q.Wm);
+    a.Grows = at<S>(p, q.grows); a.Acols = at<S>(p, h.acols[buf]); a.Gcols = at<S>(p, h.gcols);
+    a.vtime = at<unsigned long long>(p, y.vtime);
+    HIP_TRY(launch_tile_bwd<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
+  }
+  for (int l = 0; l < L - 1; ++l) {
+    const gevo_status st = tile_layer<S>(p, l, t);
+    if (st != GEVO_OK) return st;
+  }
+  p->rows_done += bt;
+  return GEVO_OK;
+}
+static_assert(GEVO_MAX_LAYERS == 3, "a deeper net needs the rows image of every hidden gradient");
 
 template <typename S>
 gevo_status begin_epoch(gevo_pop* p, int e) {
@@ -405,17 +492,28 @@ gevo_status begin_epoch(gevo_pop* p, int e) {
   g.rows = p->ws + y.xrows; g.labels = at<int32_t>(p, y.yep);
   g.blocked = y.fused;                             // the fused kernel reads rows one column block at a time
   g.res_order = y.resident;
-  HIP_TRY(launch_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
-  TransposeArgs tr{};
-  tr.src = p->ws + y.xrows; tr.dst = p->ws + y.xcols; tr.Kp = y.lay[0].Kp; tr.Bp = y.Bp; tr.T = y.T;
-  tr.blocked = y.fused;
-  tr.res_order = y.resident;
-  HIP_TRY(launch_transpose<S>(tr, p->stream, prof(p, GEVO_KERNEL_GATHER)));
+  if (y.tiles) {
+    g.cols = p->ws + y.xcols;
+    if constexpr (std::is_same<S, float>::value)
+      HIP_TRY(launch_tile_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
+  } else {
+    HIP_TRY(launch_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
+    TransposeArgs tr{};
+    tr.src = p->ws + y.xrows; tr.dst = p->ws + y.xcols; tr.Kp = y.lay[0].Kp; tr.Bp = y.Bp; tr.T = y.T;
+    tr.blocked = y.fused;
+    tr.res_order = y.resident;
+    HIP_TRY(launch_transpose<S>(tr, p->stream, prof(p, GEVO_KERNEL_GATHER)));
+  }
   HIP_TRY(launch_zero_bytes(p->ws + y.train_ce, (size_t)y.P * 8, p->stream, prof(p, GEVO_KERNEL_AUX)));
   HIP_TRY(launch_zero_bytes(p->ws + y.train_corr, (size_t)y.P * 8, p->stream, prof(p, GEVO_KERNEL_AUX)));
   // forward of step 0 for the hidden layers (the fused kernel does its own)
-  if (y.L > 1 && !y.fused) {
-    gevo_status st = forward_hidden<S>(p, at<S>(p, y.xrows), 0, y.Bp, 0);
+  if constexpr (std::is_same<S, float>::value) {
+    for (int l = 0; y.tiles && l < y.L - 1; ++l) {
+      const gevo_status st = tile_layer<S>(p, l, -1);
+      if (st != GEVO_OK) return st;
+    }
+  } else if (y.L > 1 && !y.fused) {
+    gevo_status st = forward_hidden(p, at<S>(p, y.xrows), 0, y.Bp, 0);
     if (st != GEVO_OK) return st;
   }
   p->rows_done = 0;
@@ -425,6 +523,8 @@ gevo_status begin_epoch(gevo_pop* p, int e) {
 template <typename S>
 gevo_status train_step(gevo_pop* p, int t) {
   const Layout& y = p->y;
+  if constexpr (std::is_same<S, float>::value)
+    if (y.tiles) return tile_step<S>(p, t);
   const int L = y.L;
   const int buf = t & 1, nb = buf ^ 1;
   const int64_t r0 = (int64_t)t * y.B;
@@ -465,59 +565,57 @@ gevo_status train_step(gevo_pop* p, int t) {
     if (a.Kp % kTile || a.Bp % kTile) return GEVO_E_SHAPE;
     HIP_TRY(launch_out<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_OUT_TRAIN)));
   }
-  // hidden backward GEMMs, top down (pre-update weights)
-  for (int l = L - 2; l >= 1; --l) {          // layer index l (0-based) has a hidden layer below
-    const LayerLay& q = y.lay[l];
-    const LayerLay& h = y.lay[l - 1];
-    BwdArgs<S> a{};
-    a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
-    a.Wt = at<S>(p, q.Wt);
-    a.Grows = at<S>(p, q.grows); a.gr_vs = (size_t)y.Bp * q.Np;
-    a.Acols = at<S>(p, h.acols[buf]); a.ac_vs = (size_t)h.Np * y.Bp;
-    a.Gcols = at<S>(p, h.gcols); a.gc_vs = (size_t)h.Np * y.Bp;
-    if (h.grows) { a.Grows_out = at<S>(p, h.grows); a.go_vs = (size_t)y.Bp * h.Np; }
-    a.vtime = at<unsigned long long>(p, y.vtime);
-    if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Kp != h.Np) return GEVO_E_SHAPE;
-    if constexpr (std::is_same<S, uint16_t>::value) {
+  if constexpr (std::is_same<S, uint16_t>::value) {
+    // hidden backward GEMMs, top down (pre-update weights)
+    for (int l = L - 2; l >= 1; --l) {          // layer index l (0-based) has a hidden layer below
+      const LayerLay& q = y.lay[l];
+      const LayerLay& h = y.lay[l - 1];
+      BwdArgs<S> a{};
+      a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
+      a.Wt = at<S>(p, q.Wt);
+      a.Grows = at<S>(p, q.grows); a.gr_vs = (size_t)y.Bp * q.Np;
+      a.Acols = at<S>(p, h.acols[buf]); a.ac_vs = (size_t)h.Np * y.Bp;
+      a.Gcols = at<S>(p, h.gcols); a.gc_vs = (size_t)h.Np * y.Bp;
+      if (h.grows) { a.Grows_out = at<S>(p, h.grows); a.go_vs = (size_t)y.Bp * h.Np; }
+      a.vtime = at<unsigned long long>(p, y.vtime);
+      if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Kp != h.Np) return GEVO_E_SHAPE;
       if (bwd_gemm_supported(a.Kp, a.Np, a.Bp)) {
         HIP_TRY(launch_bwd_gemm(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
         continue;
       }
+      HIP_TRY(launch_bwd<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
     }
-    HIP_TRY(launch_bwd<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
-  }
-  // hidden layers bottom up: update, then the forward of step t+1
-  const bool fwd = t + 1 < y.T;
-  for (int l = 0; l < L - 1; ++l) {
-    const LayerLay& q = y.lay[l];
-    LayerArgs<S> a{};
-    a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
-    a.Wm = at<float>(p, q.Wm); a.bias = at<float>(p, q.bias); a.mask = at<uint32_t>(p, q.mask); a.bmask = at<uint32_t>(p, q.bmask);
-    a.lr = at<float>(p, y.lrh) + (size_t)l * y.P;   // 0 for the variants that removed this layer
-    a.do_update = 1;
-    a.Gcols = at<S>(p, q.gcols); a.g_vs = (size_t)q.Np * y.Bp;
-    if (l == 0) { a.Acols = xcols_t; a.ac_vs = 0; }
-    else { a.Acols = at<S>(p, y.lay[l - 1].acols[buf]); a.ac_vs = (size_t)y.lay[l - 1].Np * y.Bp; }
-    a.do_forward = fwd ? 1 : 0;
-    a.R = y.Bp;
-    if (fwd) {
-      if (l == 0) { a.Arows = xrows_t + xstep_r; a.ar_vs = 0; }
-      else { a.Arows = at<S>(p, y.lay[l - 1].arows[nb]); a.ar_vs = (size_t)y.Bp * y.lay[l - 1].Np; }
-      a.Orows = at<S>(p, q.arows[nb]); a.or_vs = (size_t)y.Bp * q.Np;
-      a.Ocols = at<S>(p, q.acols[nb]); a.oc_vs = (size_t)q.Np * y.Bp;
-    }
-    if (q.Wt) a.Wt = at<S>(p, q.Wt);
-    a.vtime = at<unsigned long long>(p, y.vtime);
-    if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
-    if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Bp > kPassRows) return GEVO_E_SHAPE;
-    if constexpr (std::is_same<S, uint16_t>::value) {
+    // hidden layers bottom up: update, then the forward of step t+1
+    const bool fwd = t + 1 < y.T;
+    for (int l = 0; l < L - 1; ++l) {
+      const LayerLay& q = y.lay[l];
+      LayerArgs<S> a{};
+      a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
+      a.Wm = at<float>(p, q.Wm); a.bias = at<float>(p, q.bias); a.mask = at<uint32_t>(p, q.mask); a.bmask = at<uint32_t>(p, q.bmask);
+      a.lr = at<float>(p, y.lrh) + (size_t)l * y.P;   // 0 for the variants that removed this layer
+      a.do_update = 1;
+      a.Gcols = at<S>(p, q.gcols); a.g_vs = (size_t)q.Np * y.Bp;
+      if (l == 0) { a.Acols = xcols_t; a.ac_vs = 0; }
+      else { a.Acols = at<S>(p, y.lay[l - 1].acols[buf]); a.ac_vs = (size_t)y.lay[l - 1].Np * y.Bp; }
+      a.do_forward = fwd ? 1 : 0;
+      a.R = y.Bp;
+      if (fwd) {
+        if (l == 0) { a.Arows = xrows_t + xstep_r; a.ar_vs = 0; }
+        else { a.Arows = at<S>(p, y.lay[l - 1].arows[nb]); a.ar_vs = (size_t)y.Bp * y.lay[l - 1].Np; }
+        a.Orows = at<S>(p, q.arows[nb]); a.or_vs = (size_t)y.Bp * q.Np;
+        a.Ocols = at<S>(p, q.acols[nb]); a.oc_vs = (size_t)q.Np * y.Bp;
+      }
+      if (q.Wt) a.Wt = at<S>(p, q.Wt);
+      a.vtime = at<unsigned long long>(p, y.vtime);
+      if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
+      if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Bp > kPassRows) return GEVO_E_SHAPE;
       if (q.streamed) {
         a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
         HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
         continue;
       }
+      HIP_TRY(launch_layer<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
     }
-    HIP_TRY(launch_layer<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
   }
   p->rows_done += bt;
   return GEVO_OK;
@@ -705,7 +803,8 @@ gevo_status predict_layer(gevo_pop* p, const PredictBufs& b, int l, const S* aro
       return GEVO_OK;
     }
   }
-  HIP_TRY(launch_layer<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+  if constexpr (std::is_same<S, uint16_t>::value)             // full-precision hidden layers: launch_tile_fwd
+    HIP_TRY(launch_layer<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
   return GEVO_OK;
 }
 
@@ -736,6 +835,18 @@ gevo_status predict_pass(gevo_pop* p, const PredictBufs& b) {
       const LayerLay& q = y.lay[l];
       const S* ain = l == 0 ? xr : static_cast<const S*>(b.act[l - 1]);
       const size_t a_vs = l == 0 ? 0 : (size_t)kPredictChunk * y.lay[l - 1].Np;
+      if constexpr (std::is_same<S, float>::value) {
+        if (y.tiles) {
+          TileFwdArgs<S> a{};
+          a.Kp = q.Kp; a.Np = q.Np; a.R = R;
+          a.Wm = at<float>(p, q.Wm) + v0 * q.Np * q.Kp; a.bias = at<float>(p, q.bias) + v0 * q.Np;
+          a.Xrows = ain; a.xr_vs = a_vs;
+          a.Orows = static_cast<S*>(b.act[l]); a.or_vs = (size_t)kPredictChunk * q.Np;
+          a.vtime = at<unsigned long long>(p, y.vtime) + v0;
+          HIP_TRY(launch_tile_fwd<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+          continue;
+        }
+      }
       if constexpr (std::is_same<S, uint16_t>::value) {
         if (b.wbf[l] && l == y.L - 2 && q.Np == 256 && o.Kp == 256 && pred_gemm_supported(q.Kp, q.Np, R)) {
           PredGemmArgs g{};                                      // last hidden layer, one tile wide
@@ -755,6 +866,20 @@ gevo_status predict_pass(gevo_pop* p, const PredictBufs& b) {
       if (st != GEVO_OK) return st;
     }
     if (fused) continue;
+    if constexpr (std::is_same<S, float>::value) {
+      if (y.tiles) {
+        TileOutArgs<S> a{};
+        a.Kp = o.Kp; a.C = o.N;
+        a.WL = at<float>(p, o.Wm) + v0 * 32 * o.Kp; a.bias = at<float>(p, o.bias) + v0 * 32;
+        a.Arows = static_cast<const S*>(b.act[y.L - 2]); a.ar_vs = (size_t)kPredictChunk * y.lay[y.L - 2].Np;
+        a.labels = at<int32_t>(p, y.yte) + c0;
+        a.chunk0 = c0 / kOutRows; a.n_chunks_total = y.n_chunks_test;
+        a.part_ce = b.part_ce; a.part_correct = b.part_corr;
+        a.vtime = at<unsigned long long>(p, y.vtime) + v0;
+        HIP_TRY(launch_tile_pred_out<S>(a, R, b.G, p->stream, pev(p, b, GEVO_KERNEL_OUT_PREDICT)));
+        continue;
+      }
+    }
     OutArgs<S> a{};
     a.Kp = o.Kp; a.C = o.N; a.Bp = y.Bp;
     a.Wm = at<float>(p, o.Wm) + v0 * 32 * o.Kp; a.bias = at<float>(p, o.bias) + v0 * 32;
@@ -1080,7 +1205,9 @@ gevo_status gevo_pop_init(const gevo_pop_config* cfg, void* d_ws, size_t ws_byte
   g.X = d_test_x; g.y = d_test_y; g.perm = nullptr; g.n = y.n_test;
   g.d0 = y.lay[0].K; g.Kp = y.lay[0].Kp; g.B = y.n_test_pad; g.Bp = y.n_test_pad; g.T = 1;
   g.rows = p->ws + y.xte; g.labels = reinterpret_cast<int32_t*>(p->ws + y.yte);
-  hipError_t e = cfg->dtype == GEVO_BF16 ? launch_gather<uint16_t>(g, s, LaunchEv{}) : launch_gather<float>(g, s, LaunchEv{});
+  hipError_t e = cfg->dtype == GEVO_BF16 ? launch_gather<uint16_t>(g, s, LaunchEv{})
+                 : y.tiles               ? launch_tile_gather<float>(g, s, LaunchEv{})
+                                         : launch_gather<float>(g, s, LaunchEv{});
   if (e != hipSuccess) return fail(GEVO_E_HIP);
   if (launch_zero_bytes(p->ws + y.vtime, (size_t)P * 8, s, LaunchEv{}) != hipSuccess ||
       launch_zero_bytes(p->ws + y.train_ce, (size_t)P * 8, s, LaunchEv{}) != hipSuccess ||

@@ -87,6 +87,13 @@ __device__ __forceinline__ void vt_add(unsigned long long* acc, int v, uint64_t 
   if (acc && (threadIdx.x & 63) == 0) atomicAdd(acc + v, (unsigned long long)(vt_now() - t0));
 }
 
+// The same from one lane of the workgroup, its time taken for every wave: for
+// short kernels, where the waves' atomics on a few counters would be a large
+// share of the time.
+__device__ __forceinline__ void vt_add_wg(unsigned long long* acc, int v, uint64_t t0) {
+  if (acc && threadIdx.x == 0) atomicAdd(acc + v, (unsigned long long)(vt_now() - t0) * (blockDim.x / 64));
+}
+
 // An opaque copy of a value: lane-dependent indices recomputed from it cannot
 // be hoisted out of a loop, where dozens of them would stay live in registers
 // (and be spilled) for the whole loop.

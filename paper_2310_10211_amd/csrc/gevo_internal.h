@@ -210,7 +210,67 @@ struct GatherArgs {
   int blocked;                   // rows block-major, [T][Kp/32][Bp][32], instead of [T][Bp][Kp]
   int res_order;                 // (blocked only) element k of a block at position perm32(k)
   void* rows;                    // [T][Bp][Kp] S
+  void* cols;                    // launch_tile_gather only: cols image (nullable)
   int32_t* labels;               // [T][Bp]
+};
+
+// Hidden layer on tile-image operands (gevo_tiles.hip): weight gradient and
+// masked update (G set), then the forward of the next step's rows.
+template <typename S>
+struct TileLayerArgs {
+  int Kp, Np, Bp;
+  float* Wm; float* bias;        // k-blocked master [P][Kp/32][Np][32], [P][Np]
+  const uint32_t* mask;          // [P][Np][Kp/32] row words
+  const uint32_t* bmask;         // [P][Np/32]
+  const float* lr;               // [P]
+  const S* G;                    // [v][Np/32][Bp/32] blocks: gradient at this layer's output, cols image
+  const S* Acols; size_t ac_vs;  // cols image of the step's inputs (vs = 0: shared by all variants)
+  const S* Xrows; size_t xr_vs;  // rows image of the next step's inputs
+  S* Orows; S* Ocols;            // relu outputs of the next step, [v] images
+  // last hidden layer: the output layer's update (WL null: none)
+  float* WL; float* biasL;       // [P][Np/32][32][32], [P][32]
+  const uint32_t* maskL; const uint32_t* bmaskL; const float* lrL;
+  const S* Hcols;                // cols image of this layer's outputs in the step that ended
+  const S* GL;                   // [v][Bp/32] blocks of G_L, lane = class
+  const float* opdb; const double* opce; const unsigned int* opcorr;   // per row tile: see TileOutArgs
+  double* ce_acc; unsigned long long* correct_acc;
+  const uint32_t* wout;          // as in LayerArgs
+  unsigned long long* vtime;
+};
+
+template <typename S>
+struct TileOutArgs {
+  int Kp, C, Bp;
+  const float* WL; const float* bias;        // [P][Kp/32][32][32], [P][32]
+  const S* Arows; size_t ar_vs;              // rows image of the last hidden layer's outputs (ar_vs: prediction)
+  const S* Acols;                            // cols image (training)
+  const int32_t* labels;
+  float scale; const float* gscale;          // as in OutArgs
+  S* Gcols; S* Grows;                        // gradient of the last hidden layer, images (Grows nullable)
+  S* GL;                                     // [v][Bp/32] blocks of G_L, lane = class
+  float* opdb; double* opce; unsigned int* opcorr;   // per row tile: class sums of G_L, CE, hits
+  int chunk0, n_chunks_total;                // prediction: as in OutArgs
+  double* part_ce; unsigned int* part_correct;
+  unsigned long long* vtime;
+};
+
+template <typename S>
+struct TileBwdArgs {
+  int Kp, Np, Bp;
+  const float* Wm;               // k-blocked master of layer l (pre-update)
+  const S* Grows;                // [v][Bp/32][Np/32] blocks
+  const S* Acols;                // [v][Kp/32][Bp/32] blocks: activations of layer l-1
+  S* Gcols;                      // [v][Kp/32][Bp/32] blocks
+  unsigned long long* vtime;
+};
+
+template <typename S>
+struct TileFwdArgs {
+  int Kp, Np, R;
+  const float* Wm; const float* bias;
+  const S* Xrows; size_t xr_vs;  // rows image [R/32][Kp/32]
+  S* Orows; size_t or_vs;        // rows image [R/32][Np/32]
+  unsigned long long* vtime;
 };
 
 struct TransposeArgs {
@@ -235,6 +295,15 @@ template <typename S> hipError_t launch_out(const OutArgs<S>& a, int P, hipStrea
 template <typename S> hipError_t launch_bwd(const BwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_gather(const GatherArgs& a, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s, const LaunchEv& ev);
+template <typename S>
+hipError_t launch_tile_layer(const TileLayerArgs<S>& a, int P, bool upd, bool fwd, hipStream_t s, const LaunchEv& ev);
+template <typename S> hipError_t launch_tile_out(const TileOutArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
+template <typename S>
+hipError_t launch_tile_pred_out(const TileOutArgs<S>& a, int rows, int P, hipStream_t s, const LaunchEv& ev);
+template <typename S> hipError_t launch_tile_bwd(const TileBwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
+template <typename S> hipError_t launch_tile_fwd(const TileFwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
+// rows of the dataset as rows and cols images (see gevo_tiles.hip)
+template <typename S> hipError_t launch_tile_gather(const GatherArgs& a, hipStream_t s, const LaunchEv& ev);
 hipError_t launch_zero_bytes(void* p, size_t bytes, hipStream_t s, const LaunchEv& ev);
 hipError_t launch_fused2(const Fused2Args& a, int P, hipStream_t s, const LaunchEv& ev);
 // W1 master of a two-layer net: k-blocked layout <-> the fused kernel's register image

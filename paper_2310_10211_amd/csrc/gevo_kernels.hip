@@ -12,6 +12,8 @@
 // (feature contiguous) and "cols" [v][feature][b] (batch contiguous), so that
 // every MFMA operand is read along its contraction index.
 //
+// Full-precision nets with hidden layers run in gevo_tiles.hip; here fp32 is
+// left in the output-layer kernels of single-layer nets and the data movement.
 // GEMMs run on v_mfma_f32_32x32x16_bf16 (bf16 path) or v_mfma_f32_32x32x2_f32
 // (fp32 path).  Fragment layout of a 32x32xK MFMA with E elements per lane
 // (E = 8 for bf16, 1 for fp32): lane l supplies A[l%32][(l/32)*E + i] and
@@ -180,17 +182,9 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
     const S* G = a.Gcols + v * a.g_vs;
     // the gradient operand of dW first, so its loads are in flight with the
     // bias gradient's (the bias store below would otherwise hold them back)
-    if constexpr (sizeof(S) == 4) {
-      // fp32: contraction step s2 pairs batch rows s2 (lanes 0-31) and
-      // Bp/2 + s2 (lanes 32-63), so a lane's operands are contiguous
-      const S* gp = G + (size_t)(n0 + l32) * a.Bp + lh * (a.Bp / 2);
+    const S* gp = G + (size_t)(n0 + l32) * a.Bp + lh * KE;
 #pragma unroll
-      for (int s2 = 0; s2 < NG; ++s2) gf[s2] = s2 < nsteps ? gp[s2] : F{};
-    } else {
-      const S* gp = G + (size_t)(n0 + l32) * a.Bp + lh * KE;
-#pragma unroll
-      for (int s2 = 0; s2 < NG; ++s2) gf[s2] = s2 < nsteps ? O::load(gp + s2 * KM) : F{};
-    }
+    for (int s2 = 0; s2 < NG; ++s2) gf[s2] = s2 < nsteps ? O::load(gp + s2 * KM) : F{};
     // bias gradient of the 32 units: 8 lanes per unit, fixed-order reduction
     const int nl = threadIdx.x >> 3, seg = threadIdx.x & 7, per = a.Bp / 8;
     const S* gr = G + (size_t)(n0 + nl) * a.Bp + seg * per;
@@ -242,26 +236,11 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
           nmw = mrow[c + 4];
         }
         f32x16_t d0 = zero16(), d1 = zero16();
-        if constexpr (sizeof(S) == 4) {
-          // batch rows s2 and Bp/2 + s2 as above: four steps per 16-byte load
-          const float* ap = a.Acols + v * a.ac_vs + (size_t)(kb0 + c * 32 + l32) * a.Bp + lh * (a.Bp / 2);
+        const S* ap = acb + (size_t)c * 32 * a.Bp;
 #pragma unroll
-          for (int s4 = 0; s4 < NG; s4 += 4)
-            if (s4 < nsteps) {
-              const float4 x = *reinterpret_cast<const float4*>(ap + s4);
-              d0 = O::mma(gf[s4], x.x, d0);
-              d1 = O::mma(gf[s4 + 1], x.y, d1);
-              d0 = O::mma(gf[s4 + 2], x.z, d0);
-              d1 = O::mma(gf[s4 + 3], x.w, d1);
-              if ((s4 & 15) == 12) __builtin_amdgcn_sched_barrier(0);   // at most four loads ahead
-            }
-        } else {
-          const S* ap = acb + (size_t)c * 32 * a.Bp;
-#pragma unroll
-          for (int s2 = 0; s2 < NG; s2 += 2) {
-            if (s2 < nsteps) d0 = O::mma(gf[s2], O::load(ap + s2 * KM), d0);
-            if (s2 + 1 < nsteps) d1 = O::mma(gf[s2 + 1], O::load(ap + (s2 + 1) * KM), d1);
-          }
+        for (int s2 = 0; s2 < NG; s2 += 2) {
+          if (s2 < nsteps) d0 = O::mma(gf[s2], O::load(ap + s2 * KM), d0);
+          if (s2 + 1 < nsteps) d1 = O::mma(gf[s2 + 1], O::load(ap + (s2 + 1) * KM), d1);
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) dws[crow(r, lane) * DSTR + l32] = d0[r] + d1[r];
@@ -338,22 +317,6 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
       const S* ar = a.Arows + v * a.ar_vs + (size_t)(row0 + tile * 32 + l32) * Kp + kb0 + lh * KE;
       const S* br = wt + l32 * WS + lh * KE;
       int k = 0;
-      if constexpr (sizeof(S) == 4) {
-        // fp32: within each 16 inputs, step u pairs inputs u (lanes 0-31) and
-        // 8 + u (lanes 32-63), so a lane's row operands are two 16-byte loads
-        const float* ar8 = a.Arows + v * a.ar_vs + (size_t)(row0 + tile * 32 + l32) * Kp + kb0 + 8 * lh;
-        const float* br8 = wt + l32 * WS + 8 * lh;
-        for (; k + 16 <= kw; k += 16) {
-          const float4 x0 = *reinterpret_cast<const float4*>(ar8 + k);
-          const float4 x1 = *reinterpret_cast<const float4*>(ar8 + k + 4);
-          const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-#pragma unroll
-          for (int u = 0; u < 8; u += 2) {
-            acc[ti][0] = O::mma(xs[u], br8[k + u], acc[ti][0]);
-            acc[ti][1] = O::mma(xs[u + 1], br8[k + u + 1], acc[ti][1]);
-          }
-        }
-      }
       for (; k + 4 * KM <= kw; k += 4 * KM) {
         F x[4], w[4];
 #pragma unroll
@@ -1205,11 +1168,9 @@ hipError_t launch_reduce_partials(const double* part_ce, const unsigned int* par
   return hipGetLastError();
 }
 
-template hipError_t launch_layer<float>(const LayerArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_layer<uint16_t>(const LayerArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_out<float>(const OutArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_out<uint16_t>(const OutArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
-template hipError_t launch_bwd<float>(const BwdArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_bwd<uint16_t>(const BwdArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_gather<float>(const GatherArgs&, hipStream_t, const LaunchEv&);
 template hipError_t launch_gather<uint16_t>(const GatherArgs&, hipStream_t, const LaunchEv&);
