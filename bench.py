@@ -215,10 +215,11 @@ def predict_flops_per_sample(dims):
     return sum(2 * dims[l - 1] * dims[l] for l in range(1, len(dims)))
 
 
-CNN_KERNEL_SOURCES = ["gevo_device.h", "gevo_internal.h", "gevo_kernels.hip", "gevo_gemm.hip", "gevo_cnn.hip"]
+CNN_KERNEL_SOURCES = ["gevo_device.h", "gevo_internal.h", "gevo_kernels.hip", "gevo_gemm.hip", "gevo_cnn.hip",
+                      "gevo_cnn_fused.h", "gevo_cnn_fused.hip"]
 # rocprofv3 kernel-name stem -> kernel kind of the convolutional workload
 CNN_KIND_OF = {"k_cnn_stem": "stem", "k_cnn_dw": "depthwise", "k_fwd_gemm": "pointwise", "k_cnn_pool": "pool",
-               "k_out": "head", "k_cnn_pwdw": "pw_dw"}
+               "k_out": "head", "k_cnn_pwdw": "pw_dw", "k_cnn_seg": "segments"}
 
 
 def source_sha(sources=None):
@@ -706,10 +707,6 @@ def cnn_bench(args):
     for i in range(args.warmup):
         step()
         print(f"[bench] warmup {i + 1}/{args.warmup} done", file=sys.stderr, flush=True)
-    profile = not args.no_profile
-    if profile:
-        before = pop.kernel_stats()
-        pop.set_profiling(True)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(args.steps):
@@ -721,28 +718,24 @@ def cnn_bench(args):
     P, n = cfg["P"], len(y)
     value = P * n / (ms_step / 1e3)
     costs = cnn_costs(cfg, n)
-    roofline, kernel_ms = None, {}
-    if profile:
+    total_flops = sum(v[1] for v in costs.values())
+    ach = total_flops / (ms_step / 1e3) / 1e12
+    roofline = dict(bound="mfma", achieved=round(ach, 1), peak=PEAK["bf16"], unit="TFLOP/s",
+                    frac=round(ach / PEAK["bf16"], 4), kernel="k_cnn_seg (the whole pass)",
+                    algorithmic_flops=int(total_flops),
+                    traffic=traffic_for("cnn_segments", cfg["name"], CNN_KERNEL_SOURCES))
+    layer_ms = {}
+    if not args.no_profile:                       # one untimed pass, layer by layer
+        before = pop.kernel_stats()
+        pop.set_profiling(True)
+        step()
         after = pop.kernel_stats()
         pop.set_profiling(False)
-        kst = {k: (after[k][0] - before[k][0], after[k][1] - before[k][1]) for k in after}
-        kernel_ms = {k: round(v[0] / args.steps, 3) for k, v in kst.items() if v[1]}
-        dom = max((k for k in kst if kst[k][1] and k in costs), key=lambda k: kst[k][0])
-        byts, fl = costs[dom]
-        tot_s = kst[dom][0] / 1e3 / args.steps
-        launches = kst[dom][1] // args.steps
-        ach = byts / tot_s / 1e9
-        roofline = dict(bound="hbm", achieved=round(ach, 1), peak=HBM_PEAK_GBS, unit="GB/s",
-                        frac=round(ach / HBM_PEAK_GBS, 4), kernel=dom,
-                        avg_launch_us=round(tot_s / launches * 1e6, 2), launches=launches,
-                        algorithmic_bytes_per_launch=int(byts / launches),
-                        algorithmic_flops_per_launch=int(fl / launches),
-                        traffic=traffic_for("cnn_" + dom, cfg["name"], CNN_KERNEL_SOURCES))
+        layer_ms = {k: round(after[k][0] - before[k][0], 3) for k in after if after[k][1] > before[k][1]}
     cpu = None
     if not args.no_cpu:
         print("[bench] timing the CPU oracle sample", file=sys.stderr, flush=True)
         cpu = cnn_cpu_baseline(cfg, base.astype(np.float64), x, y, args.cpu_seconds)
-    total_flops = sum(v[1] for v in costs.values())
     out = {
         "metric": "variant-images/sec (prediction fitness) at P variants",
         "value": round(value, 1),
@@ -761,7 +754,7 @@ def cnn_bench(args):
                    "step": "test prediction of every variant + scores (variants built once, outside)",
                    "init_ms": round(init_ms, 1), "parallelism": "population (one GPU)"},
         "mfma_frac_of_step": round(total_flops / (ms_step / 1e3) / (PEAK["bf16"] * 1e12), 4),
-        "kernel_ms_per_step": kernel_ms,
+        "layer_by_layer_kernel_ms": layer_ms,
         "mean_test_loss": round(float(np.mean(s["test_loss"])), 4),
         "roofline": roofline,
         "cpu_baseline": cpu,

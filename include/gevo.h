@@ -494,8 +494,11 @@ gevo_status gevo_cnn_export(gevo_cnn* h, uint32_t v, float* params_out, uint8_t*
  * every kernel that gevo_cnn_predict enqueues carries a HIP event pair
  * recorded by its own dispatch on the handle's stream; gevo_cnn_kernel_stats
  * synchronises and returns, per kind, the summed kernel time in ms and the
- * launch count since the handle was created.  GEVO_E_ARG for a null handle
- * or a kind outside the enum. */
+ * launch count since the handle was created.  The kinds are single layers:
+ * where gevo_cnn_predict would otherwise run several layers as one kernel, it
+ * runs them one by one while profiling is enabled (the same roundings; sums in
+ * another order).  Time a prediction itself with profiling off.  GEVO_E_ARG
+ * for a null handle or a kind outside the enum. */
 typedef enum {
   GEVO_CNN_KERNEL_STEM = 0,        /* 3x3 stem convolution */
   GEVO_CNN_KERNEL_DEPTHWISE = 1,   /* 3x3 depthwise convolutions */

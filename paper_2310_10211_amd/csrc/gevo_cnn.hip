@@ -14,8 +14,12 @@
 //   head   global average pooling                                 (k_cnn_pool)
 //          fully connected layer, softmax cross-entropy, argmax   (k_out)
 // bf16 operands and activations, fp32 accumulation, fp32 master weights.
+// Nets whose maps fit on chip run in whole segments instead (see
+// gevo_cnn_fused.hip); the layer-by-layer kernels serve the others, and
+// predictions with kernel-level timing enabled, whose kinds are the layers.
 #include "gevo_internal.h"
 #include "gevo_device.h"
+#include "gevo_cnn_fused.h"
 #include "gevo.h"
 
 #include <hip/hip_ext.h>
@@ -577,6 +581,15 @@ struct CnnTensor {
   size_t Wm = 0, bias = 0, mask = 0, base_w = 0, base_b = 0;
   size_t pack = 0;                            // prediction copy: [P][K][N] fp32 (stem), [P][5][N] tap pairs (depthwise)
   bool packed = false, pairs = false;
+  size_t op = 0;                              // segment kernel's bf16 operand copy (stem, pointwise layers)
+  int op_ks = 0;
+};
+
+// Segments of the net that run as one kernel each: stages [s0, s1) (stage 0:
+// the stem and depthwise layer 0, stage i: pointwise i - 1 and depthwise i),
+// the last segment with the tail (last pointwise layer, pooling).
+struct CnnSegPlan {
+  int s0 = 0, s1 = 0, G = 1, x = 0, y = 0;    // images per group; bytes of the two LDS regions
 };
 
 struct CnnLayout {
@@ -588,9 +601,85 @@ struct CnnLayout {
   int nt = 0;
   CnnTensor t[2 * GEVO_CNN_MAX_BLOCKS + 2];  // stem, (dw, pw) per block, fc
   size_t act_vs = 0;                          // elements per variant of an activation buffer
+  int nseg = 0;                               // > 0: predictions run in segments
+  CnnSegPlan seg[GEVO_CNN_MAX_BLOCKS + 1];
+  int seg_images = 0;                         // images per segment launch
+  size_t mid_vs[2] = {0, 0};                  // elements per variant of the maps between segments (ping-pong)
   size_t thresh = 0, aux = 0, actA = 0, actB = 0, pooled = 0, labels = 0, part_ce = 0, part_corr = 0;
   size_t test_ce = 0, test_corr = 0, total = 0;
 };
+
+// Bytes per pixel of a map in LDS: an odd number of 16-byte pieces, so that 32
+// lanes reading 32 pixels touch every bank.
+int seg_ps(int channels) { return channels * 2 + 16; }
+
+// LDS bytes of one padded bf16 image in both copies, with room for the 16
+// elements that the last window row's reads run past it (G images: G times)
+int seg_image(int H, int W, int C) { return 2 * (((H + 2) * (W + 2) * C * 2 + 64 + 15) / 16 * 16); }
+
+// Splits the net into segments whose maps fit a CU's LDS, or leaves nseg = 0.
+// Map j (the output of depthwise layer j) is hin[j + 1] x win[j + 1] x (stem or
+// ch[j - 1]).  A segment alternates between two LDS regions: its source map
+// (or, with the stem, map 0) and every second map after it in x, the others
+// (and the padded images before the stem) in y.
+void cnn_plan_segments(CnnLayout& y) {
+  y.nseg = 0;
+  auto chan = [&](int j) { return j == 0 ? y.stem : y.ch[j - 1]; };
+  auto map_bytes = [&](int j) { return y.hin[j + 1] * y.win[j + 1] * seg_ps(chan(j)); };
+  const int image = seg_image(y.H, y.W, y.C);
+  const int64_t lds = (int64_t)kSegLds - 256;
+  for (int j = 0; j < y.nb; ++j) {
+    if (y.win[j] > 32) return;                               // a depthwise layer's input row in a wave
+    if (map_bytes(j) > lds) return;
+    if (j > 0 && chan(j - 1) != 32 && chan(j - 1) != 64 && chan(j - 1) != 128 && chan(j - 1) != 256) return;
+  }
+  const int hw_last = y.hin[y.nb] * y.win[y.nb];
+  if (hw_last > 1024) return;
+  int s0 = 0, n = 0;
+  while (true) {
+    CnnSegPlan& g = y.seg[n];
+    g = CnnSegPlan();
+    g.s0 = s0;
+    // regions of a segment of stages [s0, s1): its last map goes to memory unless the tail reads it
+    auto fits = [&](int s1, bool tail, int G, CnnSegPlan& o) {
+      int64_t r[2] = {0, s0 == 0 ? image : 0};
+      int at = 0;
+      if (s0 > 0) { r[0] = map_bytes(s0 - 1); at = 1; }      // the source map
+      for (int s = s0; s < s1; ++s) {
+        if (s + 1 == s1 && !tail) break;
+        r[at] = std::max<int64_t>(r[at], map_bytes(s));
+        at ^= 1;
+      }
+      if ((r[0] + r[1]) * G > lds) return false;
+      o.s1 = s1; o.G = G; o.x = (int)(r[0] * G); o.y = (int)(r[1] * G);
+      return true;
+    };
+    // Whole rest of the net if four images of it fit.  Otherwise up to the
+    // first map small enough that a later segment holds several images of
+    // it: the deep layers have most of the weights, which a segment reads once
+    // per group.  Otherwise as far as one image fits.
+    CnnSegPlan four;
+    bool tail = fits(y.nb, true, 4, four) || (fits(y.nb, true, 1, g) && s0 + 1 >= y.nb);
+    int s1 = s0;
+    if (!tail) {
+      for (int e = s0 + 1; e < y.nb && s1 == s0; ++e)
+        if (fits(e, false, 1, g) && (int64_t)map_bytes(e - 1) * 8 <= lds) s1 = e;
+      if (s1 == s0) tail = fits(y.nb, true, 1, g);
+    }
+    if (tail) {
+      s1 = y.nb;
+    } else if (s1 == s0) {
+      for (int e = s0 + 1; e <= y.nb; ++e)
+        if (fits(e, false, 1, g)) s1 = e;
+      if (s1 == s0) return;                                  // not even one stage
+    }
+    for (int G = 1; G <= 8; ++G) fits(s1, tail, G, g);
+    ++n;
+    if (tail) break;
+    s0 = s1;
+  }
+  y.nseg = n;
+}
 
 gevo_status cnn_layout(const gevo_cnn_config* c, int64_t n_test, CnnLayout& y) {
   if (!c || c->abi_version != GEVO_ABI_VERSION) return GEVO_E_ARG;
@@ -639,6 +728,23 @@ gevo_status cnn_layout(const gevo_cnn_config* c, int64_t n_test, CnnLayout& y) {
   if (cnn_stem_lds(y.H, y.W, y.C) > 56 * 1024) return GEVO_E_UNSUPPORTED;   // the stem stages one image in LDS
   add(ch, y.classes, 32);                             // head, in the output kernel's 32-class layout
   y.act_vs = act;
+  cnn_plan_segments(y);
+  if (y.nseg > 0) {
+    // Images per segment launch: the maps between segments about fill the
+    // 256 MB last-level cache, so what one segment writes the next one finds
+    // there; 4,096 at most, 64 at least.
+    size_t most = (size_t)ch;
+    for (int i = 0; i + 1 < y.nseg; ++i) {
+      const int j = y.seg[i].s1 - 1;                  // the map it writes
+      const size_t e = (size_t)y.hin[j + 1] * y.win[j + 1] * (size_t)(j == 0 ? y.stem : y.ch[j - 1]);
+      y.mid_vs[i & 1] = std::max(y.mid_vs[i & 1], e);
+      most = std::max(most, e);
+    }
+    y.seg_images = 4096;
+    while (y.seg_images > 64 && (size_t)y.P * y.seg_images * most * 2 > ((size_t)256 << 20)) y.seg_images /= 2;
+    while (y.seg_images > 64 && y.seg_images / 2 >= n_test) y.seg_images /= 2;
+    for (int k = 0; k < 2; ++k) y.mid_vs[k] *= (size_t)y.seg_images;
+  }
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align256(off + bytes); return at; };
   const size_t P = (size_t)y.P;
@@ -650,12 +756,17 @@ gevo_status cnn_layout(const gevo_cnn_config* c, int64_t n_test, CnnLayout& y) {
     t.base_w = take((size_t)t.Np * t.Kp * 4);
     t.base_b = take((size_t)t.Np * 4);
     if (t.packed) t.pack = take(P * (t.pairs ? 5 : t.K) * t.N * 4);
+    if (y.nseg > 0 && i + 1 < y.nt && !t.pairs) {
+      t.op_ks = i == 0 ? 3 : t.K / 16;          // (pointwise inputs are multiples of 32)
+      t.op = take(P * (size_t)(t.Np / 32) * t.op_ks * 512 * 2);
+    }
   }
   y.thresh = take(P * 4);
   y.aux = take(P * 4);                                // learning rates and bias bits the output kernel reads
-  y.actA = take(P * y.act_vs * 2);
-  y.actB = take(P * y.act_vs * 2);
-  y.pooled = take(P * kCnnChunk * ch * 2);
+  // activation maps of a 64-image chunk, or the maps between segments
+  y.actA = take(P * std::max(y.act_vs, y.mid_vs[0]) * 2);
+  y.actB = take(P * std::max(y.act_vs, y.mid_vs[1]) * 2);
+  y.pooled = take(P * (size_t)std::max(kCnnChunk, y.seg_images) * ch * 2);
   y.labels = take((size_t)y.n_chunks * kCnnChunk * 4);
   y.part_ce = take(P * y.n_chunks * 8);
   y.part_corr = take(P * y.n_chunks * 4);
@@ -748,6 +859,129 @@ LaunchEv cnn_prof(gevo_cnn* h, int kind) {
   do {                                          \
     if ((x) != hipSuccess) return GEVO_E_HIP;   \
   } while (0)
+
+namespace {
+
+// the segment kernel's operand copy of tensor i from its masters
+hipError_t cnn_pack_op(gevo_cnn* h, int i) {
+  const CnnTensor& t = h->y.t[i];
+  if (t.op_ks == 0) return hipSuccess;
+  return launch_cnn_pack_op(at<const float>(h->ws, t.Wm), t.Kp, t.Np, t.K, t.op_ks, i == 0 ? t.K / 3 : 16, h->y.P,
+                            at<uint16_t>(h->ws, t.op), h->stream);
+}
+
+gevo_status cnn_head(gevo_cnn* h, int images, int64_t first, int chunk0, int n_chunks, const LaunchEv& ev) {
+  const CnnLayout& y = h->y;
+  char* ws = h->ws;
+  const CnnTensor& tf = y.t[y.nt - 1];
+  const int ch = y.ch[y.nb - 1];
+  OutArgs<uint16_t> o{};
+  o.Kp = tf.Kp; o.C = y.classes; o.Bp = kOutRows;
+  o.Wm = at<float>(ws, tf.Wm); o.bias = at<float>(ws, tf.bias); o.mask = at<const uint32_t>(ws, tf.mask);
+  o.bmask = at<const uint32_t>(ws, y.aux); o.lr = at<const float>(ws, y.aux);
+  o.train = 0;
+  o.Arows = at<const uint16_t>(ws, y.pooled); o.ar_vs = (size_t)std::max(kCnnChunk, y.seg_images) * ch;
+  o.labels = at<const int32_t>(ws, y.labels) + first;
+  o.rows = images;                                             // padding images carry label -1
+  o.chunk0 = chunk0;
+  o.n_chunks_total = n_chunks;
+  o.part_ce = at<double>(ws, y.part_ce);
+  o.part_correct = at<unsigned int>(ws, y.part_corr);
+  CNN_HIP(launch_out<uint16_t>(o, y.P, h->stream, ev));
+  return GEVO_OK;
+}
+
+// One prediction pass in segments, seg_images images of every variant per
+// launch; one partial score per 256 images of a launch.
+gevo_status cnn_predict_segments(gevo_cnn* h) {
+  const CnnLayout& y = h->y;
+  char* ws = h->ws;
+  const int SI = y.seg_images;
+  auto chan = [&](int j) { return j == 0 ? y.stem : y.ch[j - 1]; };
+  const int launches = (int)((y.n_test + SI - 1) / SI), per = (SI + kOutRows - 1) / kOutRows;
+  const int last = (int)(y.n_test - (int64_t)(launches - 1) * SI);
+  const int n_parts = (launches - 1) * per + (last + kOutRows - 1) / kOutRows;
+  for (int c = 0; c < launches; ++c) {
+    const int64_t img0 = (int64_t)c * SI;
+    const int images = (int)std::min<int64_t>(SI, y.n_test - img0);
+    for (int k = 0; k < y.nseg; ++k) {
+      const CnnSegPlan& g = y.seg[k];
+      CnnSegArgs a{};
+      a.G = g.G;
+      a.groups = (images + g.G - 1) / g.G;
+      // several groups per workgroup once every CU has eight workgroups to run
+      a.per_wg = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)a.groups * y.P / (256 * 8)));
+      a.n_test = img0 + images; a.img0 = img0;                 // the launch's images and no further
+      a.lds = g.x + g.y;
+      int in = 0, at_y = 0;                                    // current map's region: x (0) or y (1)
+      const int off[2] = {0, g.x};
+      if (g.s0 == 0) {
+        a.stem_c = y.C;
+        a.x = h->teX; a.H = y.H; a.W = y.W;
+        a.w2_magic = cnn_magic(y.W + 2);
+        a.pad_magic = cnn_magic((y.H + 2) * (y.W + 2) * y.C);
+        a.c_magic = cnn_magic(y.C);
+        a.im = g.x;
+        a.im2 = g.x + g.G * (seg_image(y.H, y.W, y.C) / 2);
+        at_y = 1;                                              // the images
+      } else {
+        const int j = g.s0 - 1;
+        a.src = at<const uint16_t>(ws, (k - 1) & 1 ? y.actB : y.actA); a.src_vs = y.mid_vs[(k - 1) & 1];
+        a.src_px = y.hin[j + 1] * y.win[j + 1]; a.src_c = chan(j);
+        a.src_off = 0; a.src_ps = seg_ps(a.src_c); a.src_img = a.src_px * a.src_ps;
+        a.c8_magic = cnn_magic(a.src_c / 8);
+      }
+      const bool tail = k + 1 == y.nseg;
+      for (int s = g.s0; s < g.s1; ++s) {
+        CnnSegStage& t = a.st[a.nst++];
+        const CnnTensor& tp = y.t[s == 0 ? 0 : 2 * s];         // stem, or pointwise s - 1
+        const CnnTensor& td = y.t[1 + 2 * s];
+        t.S = y.stride[s]; t.KS = tp.op_ks; t.nct = chan(s) / 32;
+        t.H = y.hin[s]; t.W = y.win[s]; t.Ho = y.hin[s + 1]; t.Wo = y.win[s + 1];
+        t.wt = t.W <= 8 ? 8 : (t.W <= 16 ? 16 : 32);
+        t.wpc_log = t.nct >= 5 ? 0 : (t.nct >= 3 ? 1 : (t.nct == 2 ? 2 : 3));   // of eight waves
+        const int wpc = 1 << t.wpc_log, halves = t.wt == 32 ? 1 : 2;
+        const int most = (t.Ho + halves - 1) / halves;         // ranges of at least one output row
+        t.parts = std::max(1, std::min(most, (wpc + g.G - 1) / g.G));
+        t.q = (t.Ho + t.parts * halves - 1) / (t.parts * halves);
+        t.in = off[at_y];
+        t.ps_in = s == 0 ? 0 : seg_ps(chan(s - 1));
+        t.img_in = s == 0 ? (y.H + 2) * (y.W + 2) * y.C * 2 : t.H * t.W * t.ps_in;
+        const bool to_memory = s + 1 == g.s1 && !tail;
+        at_y ^= 1;
+        t.out = off[at_y];
+        t.ps_out = to_memory ? chan(s) * 2 : seg_ps(chan(s));
+        t.img_out = t.Ho * t.Wo * t.ps_out;
+        t.wp = at<const uint16_t>(ws, tp.op); t.pb = at<const float>(ws, tp.bias);
+        t.taps = at<const uint32_t>(ws, td.pack); t.db = at<const float>(ws, td.bias);
+        in = at_y;
+      }
+      if (tail) {
+        const CnnTensor& tp = y.t[2 * y.nb];
+        const int j = y.nb - 1;
+        a.tail = 1;
+        a.t_KS = tp.op_ks; a.t_nct = y.ch[y.nb - 1] / 32;
+        a.t_HW = y.hin[y.nb] * y.win[y.nb];
+        a.t_run = a.t_HW <= 4 ? 4 : (a.t_HW <= 8 ? 8 : 16);
+        a.t_in = off[g.s1 > g.s0 ? in : 0];
+        a.t_ps = seg_ps(chan(j)); a.t_img = a.t_HW * a.t_ps;
+        a.t_wp = at<const uint16_t>(ws, tp.op); a.t_pb = at<const float>(ws, tp.bias);
+        a.pooled = at<uint16_t>(ws, y.pooled); a.pooled_vs = (size_t)std::max(kCnnChunk, SI) * y.ch[y.nb - 1];
+      } else {
+        a.dst = at<uint16_t>(ws, k & 1 ? y.actB : y.actA); a.dst_vs = y.mid_vs[k & 1];
+      }
+      CNN_HIP(launch_cnn_seg(a, y.P, h->stream));
+    }
+    const gevo_status st = cnn_head(h, (images + 31) / 32 * 32, img0, c * per, n_parts, LaunchEv{});
+    if (st != GEVO_OK) return st;
+  }
+  CNN_HIP(launch_reduce_partials(at<double>(ws, y.part_ce), at<unsigned int>(ws, y.part_corr), y.P, n_parts,
+                                 at<double>(ws, y.test_ce), at<unsigned long long>(ws, y.test_corr), h->stream,
+                                 LaunchEv{}));
+  return GEVO_OK;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -869,6 +1103,7 @@ gevo_status gevo_cnn_init(const gevo_cnn_config* cfg, void* d_ws, size_t ws_byte
                          at<const float>(ws, t.Wm), t.Kp, t.Np, t.K, t.N, P, at<float>(ws, t.pack));
       if (hipGetLastError() != hipSuccess) return fail(GEVO_E_HIP);
     }
+    if (cnn_pack_op(h, i) != hipSuccess) return fail(GEVO_E_HIP);
   }
   // test labels per 64-image chunk, the last chunk's padding images marked -1
   std::vector<int32_t> ylab((size_t)n_test), tiles((size_t)y.n_chunks * kCnnChunk, -1);
@@ -891,6 +1126,14 @@ gevo_status gevo_cnn_predict(gevo_cnn* h) {
   hipStream_t s = h->stream;
   const int P = y.P;
   CNN_HIP(hipEventRecord(h->ev0, s));
+  if (y.nseg > 0 && !h->prof_on) {
+    const gevo_status st = cnn_predict_segments(h);
+    if (st != GEVO_OK) return st;
+    CNN_HIP(hipEventRecord(h->ev1, s));
+    h->timing_pending = true;
+    h->predicted = true;
+    return GEVO_OK;
+  }
   for (int c = 0; c < y.n_chunks; ++c) {
     // stem: test images -> A
     const CnnTensor& ts = y.t[0];
@@ -979,25 +1222,13 @@ gevo_status gevo_cnn_predict(gevo_cnn* h) {
     CnnPoolArgs pa{};
     pa.in = cur; pa.in_vs = y.act_vs;
     pa.HW = y.hin[y.nb] * y.win[y.nb]; pa.C = ch;
-    pa.out = at<uint16_t>(ws, y.pooled); pa.out_vs = (size_t)kCnnChunk * ch;
+    pa.out = at<uint16_t>(ws, y.pooled); pa.out_vs = (size_t)std::max(kCnnChunk, y.seg_images) * ch;
     ev = cnn_prof(h, GEVO_CNN_KERNEL_POOL);
     hipExtLaunchKernelGGL(k_cnn_pool, dim3((kCnnChunk * (ch / 8) + 255) / 256, P), dim3(256), 0, s, ev.start, ev.stop,
                           0, pa);
     CNN_HIP(hipGetLastError());
-    const CnnTensor& tf = y.t[y.nt - 1];
-    OutArgs<uint16_t> o{};
-    o.Kp = tf.Kp; o.C = y.classes; o.Bp = kOutRows;
-    o.Wm = at<float>(ws, tf.Wm); o.bias = at<float>(ws, tf.bias); o.mask = at<const uint32_t>(ws, tf.mask);
-    o.bmask = at<const uint32_t>(ws, y.aux); o.lr = at<const float>(ws, y.aux);
-    o.train = 0;
-    o.Arows = at<const uint16_t>(ws, y.pooled); o.ar_vs = (size_t)kCnnChunk * ch;
-    o.labels = at<const int32_t>(ws, y.labels) + (size_t)c * kCnnChunk;
-    o.rows = kCnnChunk;                                          // padding images of the last chunk carry label -1
-    o.chunk0 = c;
-    o.n_chunks_total = y.n_chunks;
-    o.part_ce = at<double>(ws, y.part_ce);
-    o.part_correct = at<unsigned int>(ws, y.part_corr);
-    CNN_HIP(launch_out<uint16_t>(o, P, s, cnn_prof(h, GEVO_CNN_KERNEL_HEAD)));
+    const gevo_status st = cnn_head(h, kCnnChunk, (int64_t)c * kCnnChunk, c, y.n_chunks, cnn_prof(h, GEVO_CNN_KERNEL_HEAD));
+    if (st != GEVO_OK) return st;
   }
   CNN_HIP(launch_reduce_partials(at<double>(ws, y.part_ce), at<unsigned int>(ws, y.part_corr), P, y.n_chunks,
                                  at<double>(ws, y.test_ce), at<unsigned long long>(ws, y.test_corr), s,
@@ -1050,6 +1281,7 @@ gevo_status gevo_cnn_remove_layer(gevo_cnn* h, uint32_t v, uint32_t layer) {
                        at<const float>(ws, t.Wm), t.N, y.P, at<uint32_t>(ws, t.pack));
     CNN_HIP(hipGetLastError());
   }
+  CNN_HIP(cnn_pack_op(h, (int)layer));                                        // the segment kernel's weights
   return GEVO_OK;
 }
 
