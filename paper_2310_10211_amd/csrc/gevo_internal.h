@@ -304,6 +304,14 @@ template <typename S> hipError_t launch_tile_bwd(const TileBwdArgs<S>& a, int P,
 template <typename S> hipError_t launch_tile_fwd(const TileFwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
 // rows of the dataset as rows and cols images (see gevo_tiles.hip)
 template <typename S> hipError_t launch_tile_gather(const GatherArgs& a, hipStream_t s, const LaunchEv& ev);
+// One layer of one variant from the device layout to the canonical one:
+// params [K][N] then the N biases, mask_out [K][N] of 0 / 1.
+struct ExportArgs {
+  int K, N, Kp, Np;
+  const float* Wm; const float* bias; const uint32_t* mask;
+  float* params; uint8_t* mask_out;
+};
+hipError_t launch_export(const ExportArgs& a, hipStream_t s);
 hipError_t launch_zero_bytes(void* p, size_t bytes, hipStream_t s, const LaunchEv& ev);
 hipError_t launch_fused2(const Fused2Args& a, int P, hipStream_t s, const LaunchEv& ev);
 // W1 master of a two-layer net: k-blocked layout <-> the fused kernel's register image

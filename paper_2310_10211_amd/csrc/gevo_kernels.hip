@@ -994,6 +994,25 @@ __global__ __launch_bounds__(256) void k_zero(uint32_t* p, size_t words) {
     p[i] = 0u;
 }
 
+// One workgroup: a 32 x 32 block of the weights, transposed through LDS.
+// Bound by the copy to the host that follows.
+__global__ __launch_bounds__(256) void k_export(ExportArgs a) {
+  __shared__ float t[32][33];
+  const int kb = blockIdx.x, n0 = 32 * blockIdx.y, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  for (int n = y; n < 32; n += 8) t[x][n] = a.Wm[((size_t)kb * a.Np + n0 + n) * 32 + x];
+  __syncthreads();
+  const int n = n0 + x;
+  if (n >= a.N) return;
+  const uint32_t m = a.mask[(size_t)n * (a.Kp / 32) + kb];
+  for (int j = y; j < 32; j += 8) {
+    const int k = 32 * kb + j;
+    if (k >= a.K) break;
+    a.params[(size_t)k * a.N + n] = t[j][x];
+    a.mask_out[(size_t)k * a.N + n] = (uint8_t)((m >> j) & 1u);
+  }
+  if (kb == 0 && y == 0) a.params[(size_t)a.K * a.N + n] = a.bias[n];
+}
+
 __global__ __launch_bounds__(256) void k_reduce_partials(const double* part_ce, const unsigned int* part_corr,
                                                          int P, int nch, double* ce_out,
                                                          unsigned long long* corr_out) {
@@ -1118,6 +1137,12 @@ hipError_t launch_zero_bytes(void* p, size_t bytes, hipStream_t s, const LaunchE
   if (words == 0) return hipSuccess;
   hipExtLaunchKernelGGL(k_zero, dim3(grid_for((int64_t)words, 256, 4096)), dim3(256), 0, s, ev.start, ev.stop, 0,
                         (uint32_t*)p, words);
+  return hipGetLastError();
+}
+
+hipError_t launch_export(const ExportArgs& a, hipStream_t s) {
+  if (a.Kp % 32 || a.Np % 32 || a.K > a.Kp || a.N > a.Np) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_export, dim3(a.Kp / 32, a.Np / 32), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
