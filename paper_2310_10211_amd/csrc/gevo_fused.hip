@@ -85,7 +85,12 @@ __device__ __forceinline__ f32x4_t mma16(uint4 a, uint4 b, f32x4_t c) {
 
 template <int HP, int BP>
 struct Fused2Lds {
-  static constexpr int NW = HP / 32;     // waves
+  static constexpr int NW = HP / 32;     // waves of a group
+  // Two groups of waves where one would leave a SIMD with a single wave and
+  // a block is short: each takes every second column block (kloop_groups).
+  static constexpr int GROUPS = HP == 128 && BP == 32 ? 2 : 1;
+  static constexpr int NT = 64 * NW * GROUPS;   // threads
+  static constexpr int XS = 36;          // row pitch of that loop's X blocks: 32 rows' 8-byte reads touch every bank
   static constexpr int BT = BP / 32;     // batch tiles
   static constexpr int NBS = BP / 16;    // contraction steps over the batch
   static constexpr int XR = 32 + 8;      // X row block [BP][32]
@@ -97,7 +102,7 @@ struct Fused2Lds {
   // region X, block loop: two X row blocks and two X column blocks
   static constexpr size_t xr = 0;
   static constexpr size_t xc = xr + 2ull * BP * XR * 2;
-  static constexpr size_t xend = xc + 2ull * 32 * XC * 2;
+  static constexpr size_t xend = GROUPS == 2 ? 8ull * 32 * XS * 2 : xc + 2ull * 32 * XC * 2;
   // region X, output-layer phase
   static constexpr size_t g2 = 0;
   static constexpr int ZGS = BP + 1;     // fp32 G2 columns [32][BP]
@@ -118,16 +123,19 @@ struct Fused2Lds {
   static constexpr size_t dbp = b2 + 32 * 4;                // [NDP][32] fp32
   static constexpr size_t rce = dbp + (size_t)NDP * 32 * 4; // [BP] fp64 per-row loss
   static constexpr size_t rco = rce + (size_t)BP * 8;       // [BP] per-row hit
-  static constexpr size_t bytes = rco + (size_t)BP * 4;
+  // second group's share of Z1
+  static constexpr size_t zp = (rco + (size_t)BP * 4 + 15) / 16 * 16;
+  static constexpr size_t bytes = GROUPS == 2 ? zp + (size_t)NW * 16 * 64 * 4 : rco + (size_t)BP * 4;
   static_assert(rce % 8 == 0, "fp64 row losses must be 8-byte aligned");
 };
 
 template <int HP, int BP>
-__global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
+__global__ __launch_bounds__((Fused2Lds<HP, BP>::NT), 1) void k_fused2(Fused2Args a) {
   using O = Op<uint16_t>;
   typedef Fused2Lds<HP, BP> Ly;
-  constexpr int NW = Ly::NW;                 // waves, one per 32 hidden units
-  constexpr int NT = 64 * NW;                // threads
+  constexpr int NW = Ly::NW;                 // waves of a group, one per 32 hidden units
+  constexpr bool GROUPS = Ly::GROUPS == 2;
+  constexpr int NT = Ly::NT;                 // threads
   constexpr int XU = (4 * BP + NT - 1) / NT; // 16-byte X chunks per thread per block
   constexpr int BT = Ly::BT;
   constexpr int NBS = Ly::NBS;
@@ -147,7 +155,9 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
   float* w2m = reinterpret_cast<float*>(smem + Ly::w2m);
   float* b2s = reinterpret_cast<float*>(smem + Ly::b2);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wv = tid >> 6;                   // wave, and its place in its group
+  const int grp = GROUPS ? __builtin_amdgcn_readfirstlane(wv / NW) : 0, wave = wv - grp * NW;
   const int v = blockIdx.x;
   const uint64_t vt0 = vt_now();
   const int Kp = a.Kp, nkb = Kp / 32;
@@ -285,6 +295,125 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
     if (fwd && td < BP) ylab = a.labels[(size_t)tf * BP + td];
   };
 
+  // Two groups: a wave's W1 block of a visit with its mask word, and the
+  // thread's piece of the X blocks of a pair of visits (rows of both, columns
+  // of both, 128 pieces of 16 bytes each).
+  struct WBlk {
+    f32x4_t w[4];
+    uint32_t m;
+  };
+  WBlk wgA, wgB;
+  u32x4_t xg;
+  auto load_w_of = [&](auto updc, int kb, int td, WBlk& d) {
+    constexpr bool upd = decltype(updc)::value;
+    const int kc = phys(kb + grp < nkb ? kb + grp : nkb - 1);    // (past the end the last block, unused)
+    const float* wp = W1 + ((size_t)kc * NW + wave) * 1024 + (td & 63) * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d.w[q] = *reinterpret_cast<const f32x4_t*>(wp + q * 256);
+    if constexpr (upd) d.m = m1[(size_t)kc * HP + wave * 32 + (td & 31)];
+  };
+  auto load_x_pair = [&](int tu, int tf, int kb, int td) {
+    const int blk = (td >> 7) & 1, kc = phys(kb + blk < nkb ? kb + blk : nkb - 1);
+    const uint16_t* p = (td >> 8) ? a.xcols + (size_t)tu * Kp * BP : a.xrows + (size_t)tf * BP * Kp;
+    xg = *reinterpret_cast<const u32x4_t*>(p + (size_t)kc * BP * 32 + (td & 127) * 8);
+  };
+  auto store_x_pair = [&](int buf, int td) {
+    const int pc = td & 127;
+    uint2* o = reinterpret_cast<uint2*>(xr + ((buf * 4 + (td >> 7)) * 32 + (pc >> 2)) * Ly::XS + (pc & 3) * 8);
+    o[0] = make_uint2(xg[0], xg[1]);
+    o[1] = make_uint2(xg[2], xg[3]);
+  };
+  auto head_groups = [&](auto updc, int tu, auto fwdc, int tf, int td) {
+    load_x_pair(tu, tf, 0, td);
+    load_w_of(updc, 0, td, wgA);
+    if (td < BP) ylab = a.labels[(size_t)tf * BP + td];
+    __builtin_amdgcn_sched_barrier(0);               // issued here, not where they are used
+  };
+  // kloop with two groups: one barrier per pair of visits, group g taking the
+  // pair's block g.  Instruction issue bounds it: a block is about 140
+  // instructions in a chain (LDS reads, two products, update, LDS reads, two
+  // products), which a wave alone on its SIMD issued every 8 cycles.  48
+  // variants of 784-128-10 at batch 32: a step's 25 blocks take 24 thousand
+  // cycles, 31 with one group, an epoch of 188 steps 2.57 and 3.22 ms; 256 such
+  // variants, bound by W1's traffic, 6.2 ms both.  (With one group, leaving out
+  // W1's loads and stores saved 4 thousand cycles, two blocks per barrier in
+  // one wave or X straight from memory none.)  The second group's Z1 is added
+  // at the end, so the forward's sum is even visits plus odd visits.
+  auto kloop_groups = [&](auto updc, int tu, auto fwdc, int tf, int td) {
+    constexpr bool upd = decltype(updc)::value, fwd = decltype(fwdc)::value;
+    const int lane = td & 63, l32 = lane & 31, lh = lane >> 5;
+    if constexpr (fwd) zacc[0] = zero16();
+    __syncthreads();                                 // the output-layer scratch shares the X buffers
+    uint4 g1r[NBS];
+    if constexpr (upd)
+#pragma unroll
+      for (int s = 0; s < NBS; ++s) g1r[s] = g1s[(wave * NBS + s) * 64 + lane];
+    store_x_pair(0, td);
+    __syncthreads();
+    auto visit = [&](int kb, bool mine, const WBlk& d, WBlk& dn) {
+      const int buf = (kb >> 1) & 1;
+      load_x_pair(tu, tf, kb + 2, td);
+      load_w_of(updc, kb + 2, td, dn);
+      __builtin_amdgcn_sched_barrier(0);
+      if (mine) {
+        const uint16_t* pc = xr + ((buf * 4 + 2 + grp) * 32 + l32) * Ly::XS + 4 * lh;
+        const uint16_t* pr = xr + ((buf * 4 + grp) * 32 + l32) * Ly::XS + 4 * lh;
+        float wnew[16];
+        if constexpr (upd) {
+          f32x16_t dacc = zero16();
+#pragma unroll
+          for (int s = 0; s < NBS; ++s) dacc = O::mma(ld2x8(pc + 16 * s, pc + 16 * s + 8), g1r[s], dacc);
+          const uint32_t mk = d.m >> (4 * lh);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = __fsub_rn(d.w[r >> 2][r & 3], __fmul_rn(lrv, dacc[r]));
+            const int keep = ((int)(mk << (31 - (8 * (r >> 2) + (r & 3))))) >> 31;   // all ones; 0: pruned, +0
+            wnew[r] = __uint_as_float(__float_as_uint(x) & (uint32_t)keep);
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4*>(W1 + (((size_t)phys(kb + grp) * NW + wave) * 4 + q) * 256 + lane * 4) =
+                make_float4(wnew[4 * q], wnew[4 * q + 1], wnew[4 * q + 2], wnew[4 * q + 3]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) wnew[r] = d.w[r >> 2][r & 3];
+        }
+        if constexpr (fwd) {
+          uint32_t pw[8];
+          to_bf16x2(wnew, pw);
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2)
+            zacc[0] = O::mma(ld2x8(pr + 16 * s2, pr + 16 * s2 + 8),
+                             make_uint4(pw[4 * s2], pw[4 * s2 + 1], pw[4 * s2 + 2], pw[4 * s2 + 3]), zacc[0]);
+        }
+      }
+      store_x_pair(buf ^ 1, td);
+      __syncthreads();
+    };
+    int kb = 0;
+    for (; kb + 4 <= nkb; kb += 4) {
+      visit(kb, true, wgA, wgB);
+      visit(kb + 2, true, wgB, wgA);
+    }
+    if (kb < nkb) visit(kb, kb + grp < nkb, wgA, wgB);
+    if (kb + 2 < nkb) visit(kb + 2, kb + 2 + grp < nkb, wgB, wgA);
+    if constexpr (fwd) {
+      f32x4_t* zp = reinterpret_cast<f32x4_t*>(smem + Ly::zp) + wave * 256 + lane;
+      if (grp == 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          zp[64 * q] = f32x4_t{zacc[0][4 * q], zacc[0][4 * q + 1], zacc[0][4 * q + 2], zacc[0][4 * q + 3]};
+      __syncthreads();
+      if (grp == 0)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4_t f = zp[64 * q];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zacc[0][4 * q + i] += f[i];
+        }
+    }
+  };
+
   // visit kb of a pass (column block phys(kb)): dW1 + update (step tu) and/or
   // forward accumulation of step tf; wc/mc hold visit kb's W1 block, wn/mn
   // receive visit kb+1's, xl receives X of visit kb+2, xs holds X of visit kb+1
@@ -409,8 +538,13 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
   };
 
   // prologue: forward of the first step
-  issue_head(off, 0, on, a.t0, tid);
-  kloop(off, 0, on, a.t0, tid);
+  if constexpr (GROUPS) {
+    head_groups(off, 0, on, a.t0, tid);
+    kloop_groups(off, 0, on, a.t0, tid);
+  } else {
+    issue_head(off, 0, on, a.t0, tid);
+    kloop(off, 0, on, a.t0, tid);
+  }
 
   for (int t = a.t0; t < a.t1; ++t) {
     // Lane-dependent indices are recomputed each step from an opaque copy of
@@ -432,6 +566,7 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
     uint4 a1p[NBS];
 #pragma unroll
     for (int T = 0; T < BT; ++T) {
+      if (GROUPS && grp != 0) continue;
       float f[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -458,7 +593,7 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
     const bool c16 = a.C <= 16;
     if (c16) {
       const int l16 = lane & 15, lq = lane >> 4, C = a.C;
-      for (int tt = wave; tt < BP / 16; tt += NW) {
+      for (int tt = wv; tt < BP / 16; tt += NT / 64) {
         f32x4_t gsv = {scale, scale, scale, scale};   // the row's output-gradient scales (issued early)
         if (a.gscale) gsv = *reinterpret_cast<const f32x4_t*>(a.gscale + ((size_t)v * BP + 16 * tt + l16) * 32 + 4 * lq);
         f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -524,22 +659,22 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
         }
         *reinterpret_cast<uint2*>(g2 + b * Ly::GS + 4 * lq) = make_uint2(gq[0], gq[1]);
       }
-    } else if (wave < BT) {
+    } else if (wv < BT) {
       f32x4_t gsv[4] = {{scale, scale, scale, scale}, {scale, scale, scale, scale}, {scale, scale, scale, scale},
                         {scale, scale, scale, scale}};   // classes 8q + 4lh + 0..3 of the row (issued early)
       if (a.gscale)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          gsv[q] = *reinterpret_cast<const f32x4_t*>(a.gscale + ((size_t)v * BP + 32 * wave + l32) * 32 + 8 * q + 4 * lh);
+          gsv[q] = *reinterpret_cast<const f32x4_t*>(a.gscale + ((size_t)v * BP + 32 * wv + l32) * 32 + 8 * q + 4 * lh);
       f32x16_t c0 = zero16(), c1 = zero16();
       const uint16_t* ap = w2 + l32 * Ly::W2S + 8 * lh;
-      const uint16_t* bp = a1 + (32 * wave + l32) * Ly::AS + 8 * lh;
+      const uint16_t* bp = a1 + (32 * wv + l32) * Ly::AS + 8 * lh;
 #pragma unroll
       for (int s = 0; s < HP / 16; s += 2) {
         c0 = O::mma(O::load(ap + 16 * s), O::load(bp + 16 * s), c0);
         c1 = O::mma(O::load(ap + 16 * s + 16), O::load(bp + 16 * s + 16), c1);
       }
-      const int b = 32 * wave + l32, C = a.C, y = yl[b];
+      const int b = 32 * wv + l32, C = a.C, y = yl[b];
       const bool rvalid = y >= 0;
       float z[16];
       float ml = -INFINITY, bv = -INFINITY;
@@ -601,14 +736,16 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
     {
       const int c = tid & 31, part = tid >> 5;       // Ly::NDP parts
       float sp = 0.0f;
-      if (!c16 || c < 16)
+      if ((!c16 || c < 16) && part < Ly::NDP)
         for (int r = part; r < BP; r += Ly::NDP) sp += zg[c * Ly::ZGS + r];
-      dbp[part * 32 + c] = sp;
+      if (part < Ly::NDP) dbp[part * 32 + c] = sp;
     }
     // the next pass's first blocks, W1 words and labels can load from here on
     // (the last step's pass also runs a forward, of a valid batch, whose result is unused)
     const int tf = t + 1 < a.T ? t + 1 : t;
-    issue_head(on, t, on, tf, tid_step);
+    if constexpr (GROUPS) head_groups(on, t, on, tf, tid_step);
+    else issue_head(on, t, on, tf, tid_step);
+    if (!GROUPS || grp == 0) {                       // (the second group has no units of its own)
     // ---- dW2 = G2^T A1 (classes x hidden), A1 from registers
     f32x16_t d2 = zero16();
 #pragma unroll
@@ -672,21 +809,24 @@ __global__ __launch_bounds__(2 * HP, 1) void k_fused2(Fused2Args a) {
         *reinterpret_cast<float4*>(w2row + (((2 * q + lh) ^ sw) << 2)) =
             make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
     }
+    }
     // ---- dW1 + masked SGD on W1 + forward of the next step
     int tid_pass;
     asm volatile("v_mov_b32 %0, %1" : "=v"(tid_pass) : "v"(tid));
-    kloop(on, t, on, tf, tid_pass);
+    if constexpr (GROUPS) kloop_groups(on, t, on, tf, tid_pass);
+    else kloop(on, t, on, tf, tid_pass);
   }
   __syncthreads();                             // the last step's partial sums
   finish_out();
   // ---- write back the resident state
+  if (!GROUPS || grp == 0)
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const float4 f = *reinterpret_cast<const float4*>(w2row + (((2 * q + lh) ^ sw) << 2));
 #pragma unroll
     for (int i = 0; i < 4; ++i) W2[((size_t)wave * 32 + crow(4 * q + i, lane)) * 32 + l32] = f4get(f, i);
   }
-  if (lh == 0) a.b1[(size_t)v * HP + n] = b1v;
+  if (lh == 0 && grp == 0) a.b1[(size_t)v * HP + n] = b1v;
   if (tid < 32) a.b2[(size_t)v * 32 + tid] = b2s[tid];
   if (tid == tot_tid) {
     a.ce_acc[v] = ce_tot;
@@ -714,7 +854,7 @@ static hipError_t launch_f2(const Fused2Args& a, int P, hipStream_t s, const Lau
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr = true;
   }
-  hipExtLaunchKernelGGL((k_fused2<HP, BP>), dim3(P), dim3(2 * HP), lds, s, ev.start, ev.stop, 0, a);
+  hipExtLaunchKernelGGL((k_fused2<HP, BP>), dim3(P), dim3(Fused2Lds<HP, BP>::NT), lds, s, ev.start, ev.stop, 0, a);
   return hipGetLastError();
 }
 
