@@ -130,17 +130,39 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
   }
   if (out_lds(y.lay[y.L - 1].Kp, y.Bp, y.elt, pad) > kLdsBudget) return GEVO_E_UNSUPPORTED;
   y.fused = y.L == 2 && c->dtype == GEVO_BF16 && fused2_lds_bytes(y.lay[0].Np, y.Bp) > 0;
-  // Full-precision nets with a hidden layer run on the tile-image kernels in
-  // training and prediction at every size (one epoch and a prediction of 64
-  // variants of 784-256-10: 78 ms with row-major operands, 46 ms; 4 variants
-  // of 784-128-10 on 2,048 rows: 5.0 and 2.7 ms).
-  y.tiles = y.L > 1 && c->dtype == GEVO_F32;
   y.resident = y.fused && res2_supported(y.lay[0].Kp, y.lay[0].Np, y.Bp, (int)c->dims[2]) && resident_requested();
+  bool all_streamed = true;
   for (int l = 0; l + 1 < y.L; ++l) {
     LayerLay& q = y.lay[l];
     q.pred = c->dtype == GEVO_BF16 && pred_gemm_supported(q.Kp, q.Np, kOutRows);
     q.streamed = c->dtype == GEVO_BF16 && !y.fused && stream_layer_supported(q.Kp, q.Np, y.Bp, y.Bp);
-    y.images = y.images || q.streamed;
+    all_streamed = all_streamed && q.streamed;
+  }
+  // Tile-image kernels.  Full-precision nets with a hidden layer use them in
+  // training and prediction at every size (one epoch and a prediction of 64
+  // variants of 784-256-10: 78 ms with row-major operands, 44 ms; 4 variants of
+  // 784-128-10 on 2,048 rows: 5.0 and 2.0 ms).  bf16 nets use them in training
+  //  - where the fused kernel does not take the net and the streaming kernel
+  //    not every hidden layer (an epoch of 24 variants of 784-300-100-10, batch
+  //    100: 5.3 ms with row-major operands, 2.8; 256 of 784-512-10, batch 128:
+  //    23.3 and 16.7; 250 of 1000-300-10, batch 200: 12.2 and 6.6);
+  //  - where those would leave most of the chip idle: they give a workgroup a
+  //    variant or 128 units, these 32 units, so up to one workgroup per CU.
+  //    Streamed: 16 variants of 3072-512-10, batch 128, 20 steps: 2.2 and 1.4
+  //    ms; 128 of them 8.3 and 10.4.  Fused, 47 steps of batch 128: 32
+  //    variants of 784-256-10 2.09 and 1.42 ms, 64 of 784-128-10 1.64 and 1.40,
+  //    100 of 784-256-10 2.10 and 3.29; its step is short for few inputs (16 of
+  //    100-256-10: 0.66 and 0.85) and at smaller batches (48 of 784-128-10,
+  //    batch 32: 1.3 and 2.0), so from 512 inputs and 97 rows up.
+  int widest = 0;
+  for (int l = 0; l + 1 < y.L; ++l) widest = std::max(widest, y.lay[l].Np);
+  const bool few = (int64_t)y.P * (widest / 32) <= 256;
+  y.tiles = y.L > 1 && (c->dtype == GEVO_F32 ||
+                        (y.fused ? few && y.Bp == 128 && y.lay[0].Kp >= 512 && !y.resident : few || !all_streamed));
+  if (y.tiles) y.fused = false;
+  for (int l = 0; l + 1 < y.L; ++l) {
+    if (y.tiles) y.lay[l].streamed = false;
+    y.images = y.images || y.lay[l].streamed;
   }
   y.images = y.images || y.fused;
   size_t off = 0;
@@ -399,12 +421,8 @@ gevo_status forward_layer(gevo_pop* p, int l, const uint16_t* arows0, size_t ar0
   a.vtime = at<unsigned long long>(p, y.vtime);
   if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
   if (a.Kp % kTile || a.Np % kTile || a.R % kTile || a.R <= 0) return GEVO_E_SHAPE;
-  if (q.streamed) {
-    a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
-    HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
-    return GEVO_OK;
-  }
-  HIP_TRY(launch_layer<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
+  a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
+  HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
   return GEVO_OK;
 }
 
@@ -519,8 +537,7 @@ gevo_status begin_epoch(gevo_pop* p, int e) {
   g.res_order = y.resident;
   if (y.tiles) {
     g.cols = p->ws + y.xcols;
-    if constexpr (std::is_same<S, float>::value)
-      HIP_TRY(launch_tile_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
+    HIP_TRY(launch_tile_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
   } else {
     HIP_TRY(launch_gather<S>(g, p->stream, prof(p, GEVO_KERNEL_GATHER)));
     TransposeArgs tr{};
@@ -531,14 +548,17 @@ gevo_status begin_epoch(gevo_pop* p, int e) {
   }
   HIP_TRY(launch_zero_bytes(p->ws + y.train_ce, (size_t)y.P * 8 * 2, p->stream, prof(p, GEVO_KERNEL_AUX)));   // and train_corr
   // forward of step 0 for the hidden layers (the fused kernel does its own)
-  if constexpr (std::is_same<S, float>::value) {
-    for (int l = 0; y.tiles && l < y.L - 1; ++l) {
+  if (y.tiles) {
+    for (int l = 0; l < y.L - 1; ++l) {
       const gevo_status st = tile_layer<S>(p, l, -1);
       if (st != GEVO_OK) return st;
     }
-  } else if (y.L > 1 && !y.fused) {
-    gevo_status st = forward_hidden(p, at<S>(p, y.xrows), 0, y.Bp, 0);
-    if (st != GEVO_OK) return st;
+  }
+  if constexpr (std::is_same<S, uint16_t>::value) {
+    if (y.L > 1 && !y.fused && !y.tiles) {
+      gevo_status st = forward_hidden(p, at<S>(p, y.xrows), 0, y.Bp, 0);
+      if (st != GEVO_OK) return st;
+    }
   }
   p->rows_done = 0;
   return GEVO_OK;
@@ -547,8 +567,7 @@ gevo_status begin_epoch(gevo_pop* p, int e) {
 template <typename S>
 gevo_status train_step(gevo_pop* p, int t) {
   const Layout& y = p->y;
-  if constexpr (std::is_same<S, float>::value)
-    if (y.tiles) return tile_step<S>(p, t);
+  if (y.tiles) return tile_step<S>(p, t);
   const int L = y.L;
   const int buf = t & 1, nb = buf ^ 1;
   const int64_t r0 = (int64_t)t * y.B;
@@ -603,11 +622,7 @@ gevo_status train_step(gevo_pop* p, int t) {
       if (h.grows) { a.Grows_out = at<S>(p, h.grows); a.go_vs = (size_t)y.Bp * h.Np; }
       a.vtime = at<unsigned long long>(p, y.vtime);
       if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Kp != h.Np) return GEVO_E_SHAPE;
-      if (bwd_gemm_supported(a.Kp, a.Np, a.Bp)) {
-        HIP_TRY(launch_bwd_gemm(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
-        continue;
-      }
-      HIP_TRY(launch_bwd<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
+      HIP_TRY(launch_bwd_gemm(a, y.P, p->stream, prof(p, GEVO_KERNEL_BWD)));
     }
     // hidden layers bottom up: update, then the forward of step t+1
     const bool fwd = t + 1 < y.T;
@@ -633,12 +648,8 @@ gevo_status train_step(gevo_pop* p, int t) {
       a.vtime = at<unsigned long long>(p, y.vtime);
       if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
       if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Bp > kPassRows) return GEVO_E_SHAPE;
-      if (q.streamed) {
-        a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
-        HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
-        continue;
-      }
-      HIP_TRY(launch_layer<S>(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
+      a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
+      HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
     }
   }
   p->rows_done += bt;

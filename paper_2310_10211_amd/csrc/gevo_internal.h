@@ -292,7 +292,6 @@ struct LaunchEv {
 hipError_t launch_init(const InitArgs& a, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_layer(const LayerArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_out(const OutArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
-template <typename S> hipError_t launch_bwd(const BwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_gather(const GatherArgs& a, hipStream_t s, const LaunchEv& ev);
 template <typename S> hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s, const LaunchEv& ev);
 template <typename S>
@@ -328,9 +327,9 @@ hipError_t launch_pred_gemm(const PredGemmArgs& a, hipStream_t s, const LaunchEv
 // k-blocked fp32 master [P][Kp/32][Np][32] -> bf16 [P][Np][Kp] (Np % 256 == 0)
 hipError_t launch_wt_bf16(const float* Wm, uint16_t* Wb, int P, int Kp, int Np, hipStream_t s, const LaunchEv& ev);
 // bf16 hidden layer over one training batch (update and/or forward of the
-// next batch) streaming the fp32 master once; shapes outside these use k_layer
+// next batch) streaming the fp32 master once; nets outside these use the tile-image kernels
 bool stream_layer_supported(int Kp, int Np, int Bp, int R);
-// bf16 backward GEMM of a hidden layer (per variant, LDS-tiled); other shapes use k_bwd
+// bf16 backward GEMM of a hidden layer (per variant, LDS-tiled)
 bool bwd_gemm_supported(int Kp, int Np, int Bp);
 hipError_t launch_bwd_gemm(const BwdArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev);
 hipError_t launch_stream_layer(const LayerArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev);

@@ -240,32 +240,20 @@ __global__ __launch_bounds__(256) void k_init4(InitArgs a, int per) {
 }
 
 // ------------------------------------------------------------ hidden layer
-// Workgroup (n-tile of 32 output units, variant v); four waves.  The inputs
-// k are processed in blocks of KB columns (the block's operand copy of W fits
-// in LDS).  Update (do_update), per 32-wide chunk c of a block, each wave
-// streaming its own chunks with the next chunk's weights already in flight:
-//   dW^T[n][k] = sum_b G[n][b] * A[k][b]          (MFMA, contraction = batch)
-// staged through LDS, then lane (row n, 16 columns) applies
-//   W[n][k]    = mask ? fl(W - fl(lr * dW)) : +0   (fp32 master, float4 in place)
-// and b[n] -= lr * sum_b G[n][b].  The updated block stays in LDS as an
-// operand, so the forward pass of the next step runs without re-reading W:
-//   Z[r][n] = sum_k A_next[r][k] * W[n][k] + b[n],  A_out = relu(Z)  (MFMA)
-// Without do_update a block is loaded from the master (forward only).
-template <typename S, int BPMAX>
+// Prediction rows of the shapes that the GEMM kernels do not take.  Workgroup
+// (n-tile of 32 output units, variant v); four waves.  The inputs k are
+// processed in blocks of KB columns (the block's operand copy of W fits in LDS):
+//   O[r][n] = relu(sum_k A[r][k] * W[n][k] + b[n])                        (MFMA)
+template <typename S>
 __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
   using O = Op<S>;
   using F = typename O::Frag;
   constexpr int KM = O::KM, KE = O::KE;
-  constexpr int NG = BPMAX / KM;
-  constexpr int TPW = BPMAX / 128;                   // row tiles per wave in a forward pass
-  constexpr int PASS = BPMAX;                        // rows per forward pass
-  constexpr int DSTR = 36;                           // fp32 staging row stride (16-byte aligned rows)
-  constexpr int SSTR = 32 + O::PAD;
+  constexpr int PASS = 128;                          // rows per pass, a 32-row tile per wave
   extern __shared__ __align__(16) char smem[];
   __shared__ float bias_l[32];
   const int KB = a.KB, WS = KB + O::PAD;
   S* wt = reinterpret_cast<S*>(smem);                                // [32][WS] operand tile
-  float* stage = reinterpret_cast<float*>(smem + (size_t)32 * WS * sizeof(S));   // [4][32][DSTR]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
   const int n0 = blockIdx.x * 32, v = blockIdx.y;
@@ -274,109 +262,18 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
     vt_add(a.vtime, v, vt0);
     return;
   }
-  const int Kp = a.Kp, Np = a.Np, kwords = Kp / 32;
-  float* Wv = a.Wm + (size_t)v * Np * Kp;                     // this variant, k-blocked
-  const uint32_t* mk = a.mask + ((size_t)v * Np + n0) * kwords;
-  const float lrv = a.lr[v];
-  const int nsteps = a.Bp / KM;
-  float* dws = stage + wave * 32 * DSTR;
-  const int rn = lane >> 1, cs = (lane & 1) * 16;            // update ownership: row rn, columns cs..cs+15
-
-  F gf[NG];
-  if (a.do_update) {
-    const S* G = a.Gcols + v * a.g_vs;
-    // the gradient operand of dW first, so its loads are in flight with the
-    // bias gradient's (the bias store below would otherwise hold them back)
-    const S* gp = G + (size_t)(n0 + l32) * a.Bp + lh * KE;
-#pragma unroll
-    for (int s2 = 0; s2 < NG; ++s2) gf[s2] = s2 < nsteps ? O::load(gp + s2 * KM) : F{};
-    // bias gradient of the 32 units: 8 lanes per unit, fixed-order reduction
-    const int nl = threadIdx.x >> 3, seg = threadIdx.x & 7, per = a.Bp / 8;
-    const S* gr = G + (size_t)(n0 + nl) * a.Bp + seg * per;
-    float s = 0.0f;
-    for (int b = 0; b < per; ++b) s += O::to_f32(gr[b]);
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    s += __shfl_xor(s, 4);
-    if (seg == 0) {
-      const float bo = a.bias[(size_t)v * Np + n0 + nl];
-      const bool bk = (a.bmask[(size_t)v * (Np / 32) + blockIdx.x] >> nl) & 1u;   // n0 = 32 blockIdx.x
-      const float bn = bk ? __fsub_rn(bo, __fmul_rn(lrv, s)) : 0.0f;
-      a.bias[(size_t)v * Np + n0 + nl] = bn;
-      bias_l[nl] = bn;
-    }
-  } else if (threadIdx.x < 32) {
-    bias_l[threadIdx.x] = a.bias[(size_t)v * Np + n0 + threadIdx.x];
-  }
+  const int Kp = a.Kp, Np = a.Np;
+  const float* Wv = a.Wm + (size_t)v * Np * Kp;               // this variant, k-blocked
+  if (threadIdx.x < 32) bias_l[threadIdx.x] = a.bias[(size_t)v * Np + n0 + threadIdx.x];
 
   const int nblk = (Kp + KB - 1) / KB;
-  const int R = a.do_forward ? a.R : 0;
-  const int npass = a.do_forward ? (R + PASS - 1) / PASS : 0;
+  const int R = a.R;
+  const int npass = (R + PASS - 1) / PASS;
 
-  // ---- fill the LDS operand tile with block blk (update or plain load), plus Wt
-  auto fill = [&](int blk, bool upd) {
+  // ---- fill the LDS operand tile with block blk
+  auto fill = [&](int blk) {
     const int kb0 = blk * KB;
     const int kw = min(KB, Kp - kb0);
-    const int nchb = kw / 32;
-    if (upd) {
-      // row rn of the tile in 32-column chunk c of this block
-      auto wptr = [&](int c) { return Wv + ((size_t)(kb0 / 32 + c) * Np + n0 + rn) * 32 + cs; };
-      const uint32_t* mrow = mk + (size_t)rn * kwords + kb0 / 32;
-      const S* acb = a.Acols + v * a.ac_vs + (size_t)(kb0 + l32) * a.Bp + lh * KE;
-      float4 nx[4];
-      uint32_t nmw = 0;
-      if (wave < nchb) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) nx[u] = *reinterpret_cast<const float4*>(wptr(wave) + 4 * u);
-        nmw = mrow[wave];
-      }
-      for (int c = wave; c < nchb; c += 4) {
-        float4 w4[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) w4[u] = nx[u];
-        const uint32_t mw = nmw;
-        if (c + 4 < nchb) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) nx[u] = *reinterpret_cast<const float4*>(wptr(c + 4) + 4 * u);
-          nmw = mrow[c + 4];
-        }
-        f32x16_t d0 = zero16(), d1 = zero16();
-        const S* ap = acb + (size_t)c * 32 * a.Bp;
-#pragma unroll
-        for (int s2 = 0; s2 < NG; s2 += 2) {
-          if (s2 < nsteps) d0 = O::mma(gf[s2], O::load(ap + s2 * KM), d0);
-          if (s2 + 1 < nsteps) d1 = O::mma(gf[s2 + 1], O::load(ap + (s2 + 1) * KM), d1);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dws[crow(r, lane) * DSTR + l32] = d0[r] + d1[r];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        float dw[16];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float4 t = *reinterpret_cast<const float4*>(dws + rn * DSTR + cs + 4 * u);
-          dw[4 * u] = t.x; dw[4 * u + 1] = t.y; dw[4 * u + 2] = t.z; dw[4 * u + 3] = t.w;
-        }
-        float wn[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float w = (i & 3) == 0 ? w4[i >> 2].x : (i & 3) == 1 ? w4[i >> 2].y : (i & 3) == 2 ? w4[i >> 2].z : w4[i >> 2].w;
-          const bool keep = (mw >> (cs + i)) & 1u;
-          wn[i] = keep ? __fsub_rn(w, __fmul_rn(lrv, dw[i])) : 0.0f;
-        }
-        float* wdst = wptr(c);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          *reinterpret_cast<float4*>(wdst + 4 * u) = make_float4(wn[4 * u], wn[4 * u + 1], wn[4 * u + 2], wn[4 * u + 3]);
-        S* od = wt + rn * WS + c * 32 + cs;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) od[i] = O::from_f32(wn[i]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      }
-    } else {
       const int q = kw / 4;                               // float4 per row
       for (int i = threadIdx.x; i < 32 * q; i += 256 * 4) {
         float4 w4[4];
@@ -398,107 +295,52 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
           }
         }
       }
-    }
     __syncthreads();
-    if (a.Wt) {
-      // transposed operand copy [k][n] for the backward of the layer above
-      for (int k = threadIdx.x >> 1; k < kw; k += 128) {
-        const int half = threadIdx.x & 1;
-        S* dst = a.Wt + (size_t)v * Kp * Np + (size_t)(kb0 + k) * Np + n0 + half * 16;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) dst[i] = wt[(half * 16 + i) * WS + k];
-      }
-    }
   };
 
-  // ---- forward over block blk for rows [row0, row0 + 32*ntiles); two accumulator chains per tile
-  auto forward = [&](int blk, int row0, int ntiles, f32x16_t (&acc)[TPW][2]) {
+  // ---- forward over block blk for the wave's tile of rows; two accumulator chains
+  auto forward = [&](int blk, int row0, int ntiles, f32x16_t (&acc)[2]) {
+    if (wave >= ntiles) return;
     const int kb0 = blk * KB;
     const int kw = min(KB, Kp - kb0);
+    const S* ar = a.Arows + v * a.ar_vs + (size_t)(row0 + wave * 32 + l32) * Kp + kb0 + lh * KE;
+    const S* br = wt + l32 * WS + lh * KE;
+    int k = 0;
+    for (; k + 4 * KM <= kw; k += 4 * KM) {
+      F x[4], w[4];
 #pragma unroll
-    for (int ti = 0; ti < TPW; ++ti) {
-      const int tile = wave + 4 * ti;
-      if (tile >= ntiles) continue;
-      const S* ar = a.Arows + v * a.ar_vs + (size_t)(row0 + tile * 32 + l32) * Kp + kb0 + lh * KE;
-      const S* br = wt + l32 * WS + lh * KE;
-      int k = 0;
-      for (; k + 4 * KM <= kw; k += 4 * KM) {
-        F x[4], w[4];
+      for (int u = 0; u < 4; ++u) { x[u] = O::load(ar + k + u * KM); w[u] = O::load(br + k + u * KM); }
+      acc[0] = O::mma(x[0], w[0], acc[0]);
+      acc[1] = O::mma(x[1], w[1], acc[1]);
+      acc[0] = O::mma(x[2], w[2], acc[0]);
+      acc[1] = O::mma(x[3], w[3], acc[1]);
+    }
+    for (; k < kw; k += KM) acc[0] = O::mma(O::load(ar + k), O::load(br + k), acc[0]);
+  };
+
+  // ---- epilogue: bias + ReLU
+  auto epilogue = [&](int row0, int ntiles, const f32x16_t (&acc)[2]) {
+    if (wave >= ntiles) return;
+    const float bn = bias_l[l32];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { x[u] = O::load(ar + k + u * KM); w[u] = O::load(br + k + u * KM); }
-        acc[ti][0] = O::mma(x[0], w[0], acc[ti][0]);
-        acc[ti][1] = O::mma(x[1], w[1], acc[ti][1]);
-        acc[ti][0] = O::mma(x[2], w[2], acc[ti][0]);
-        acc[ti][1] = O::mma(x[3], w[3], acc[ti][1]);
-      }
-      for (; k < kw; k += KM) acc[ti][0] = O::mma(O::load(ar + k), O::load(br + k), acc[ti][0]);
+    for (int r = 0; r < 16; ++r) {
+      const float z = (acc[0][r] + acc[1][r]) + bn;
+      a.Orows[v * a.or_vs + (size_t)(row0 + wave * 32 + crow(r, lane)) * Np + n0 + l32] =
+          O::from_f32(z > 0.0f ? z : 0.0f);
     }
   };
 
-  // ---- epilogue: bias + ReLU, rows store, transposed store staged in LDS
-  auto epilogue = [&](int row0, int ntiles, f32x16_t (&acc)[TPW][2]) {
-    S* sw = reinterpret_cast<S*>(dws);                      // [32][SSTR] per wave
-#pragma unroll
-    for (int ti = 0; ti < TPW; ++ti) {
-      const int tile = wave + 4 * ti;
-      if (tile < ntiles) {                                  // wave-uniform
-        const float bn = bias_l[l32];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rl = crow(r, lane);
-          const float z = (acc[ti][0][r] + acc[ti][1][r]) + bn;
-          const S sv = O::from_f32(z > 0.0f ? z : 0.0f);
-          a.Orows[v * a.or_vs + (size_t)(row0 + tile * 32 + rl) * Np + n0 + l32] = sv;
-          sw[l32 * SSTR + rl] = sv;                        // [n][row]
-        }
-        if (a.Ocols) {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          const int nl = lane >> 1, half = lane & 1;
-          S* dst = a.Ocols + v * a.oc_vs + (size_t)(n0 + nl) * R + row0 + tile * 32 + half * 16;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) dst[i] = sw[nl * SSTR + half * 16 + i];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      }
-    }
-  };
-
-  if (nblk == 1) {
-    fill(0, a.do_update != 0);
-    __syncthreads();
-    for (int pass = 0; pass < npass; ++pass) {
-      const int row0 = pass * PASS;
-      const int ntiles = min(PASS, R - row0) / 32;
-      f32x16_t acc[TPW][2];
-#pragma unroll
-      for (int ti = 0; ti < TPW; ++ti) { acc[ti][0] = zero16(); acc[ti][1] = zero16(); }
-      forward(0, row0, ntiles, acc);
-      epilogue(row0, ntiles, acc);
-    }
-  } else if (npass == 0) {
+  if (nblk == 1) fill(0);
+  for (int pass = 0; pass < npass; ++pass) {
+    const int row0 = pass * PASS;
+    const int ntiles = min(PASS, R - row0) / 32;
+    f32x16_t acc[2] = {zero16(), zero16()};
     for (int blk = 0; blk < nblk; ++blk) {
-      fill(blk, a.do_update != 0);
-      __syncthreads();
+      if (nblk > 1) fill(blk);
+      forward(blk, row0, ntiles, acc);
+      if (nblk > 1) __syncthreads();
     }
-  } else {
-    for (int pass = 0; pass < npass; ++pass) {
-      const int row0 = pass * PASS;
-      const int ntiles = min(PASS, R - row0) / 32;
-      f32x16_t acc[TPW][2];
-#pragma unroll
-      for (int ti = 0; ti < TPW; ++ti) { acc[ti][0] = zero16(); acc[ti][1] = zero16(); }
-      for (int blk = 0; blk < nblk; ++blk) {
-        fill(blk, a.do_update != 0 && pass == 0);
-        __syncthreads();
-        forward(blk, row0, ntiles, acc);
-        __syncthreads();
-      }
-      epilogue(row0, ntiles, acc);
-    }
+    epilogue(row0, ntiles, acc);
   }
   vt_add(a.vtime, v, vt0);
 }
@@ -984,38 +826,6 @@ __global__ __launch_bounds__(256) void k_out_upd(OutArgs<S> a) {
   vt_add(a.vtime, v, vt0);
 }
 
-// ------------------------------------------------------- hidden backward GEMM
-// G_{l-1}[k][b] = (sum_n W_l[n][k] G_l[b][n]) * [A_{l-1}[k][b] > 0]; one
-// 32x32 output tile per wave, operands straight from L2.
-template <typename S>
-__global__ __launch_bounds__(256) void k_bwd(BwdArgs<S> a) {
-  using O = Op<S>;
-  constexpr int KM = O::KM, KE = O::KE;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l32 = lane & 31, lh = lane >> 5;
-  const int v = blockIdx.y;
-  const uint64_t vt0 = vt_now();
-  const int tb = a.Bp / 32;
-  const int t = blockIdx.x * 4 + wave;
-  if (t >= (a.Kp / 32) * tb) return;
-  const int kt = t / tb, bt = t % tb;
-  const S* wr = a.Wt + (size_t)v * a.Kp * a.Np + (size_t)(kt * 32 + l32) * a.Np + lh * KE;
-  const S* gr = a.Grows + v * a.gr_vs + (size_t)(bt * 32 + l32) * a.Np + lh * KE;
-  f32x16_t acc = zero16();
-  for (int n = 0; n < a.Np; n += KM) acc = O::mma(O::load(wr + n), O::load(gr + n), acc);
-  const S* acv = a.Acols + v * a.ac_vs;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int k = kt * 32 + crow(r, lane);
-    const int b = bt * 32 + l32;
-    const float av = O::to_f32(acv[(size_t)k * a.Bp + b]);
-    const S g = O::from_f32(av > 0.0f ? acc[r] : 0.0f);
-    a.Gcols[v * a.gc_vs + (size_t)k * a.Bp + b] = g;
-    if (a.Grows_out) a.Grows_out[v * a.go_vs + (size_t)b * a.Kp + k] = g;
-  }
-  vt_add(a.vtime, v, vt0);
-}
-
 // ------------------------------------------------------------- data movement
 // rows[t][b][k] = X[perm[t*B + b]][k] (zero for k >= d0, b >= b_t, b >= B),
 // labels[t][b] = y[...] or -1.
@@ -1156,11 +966,8 @@ hipError_t launch_init(const InitArgs& a, hipStream_t s, const LaunchEv& ev) {
   return hipGetLastError();
 }
 
-size_t layer_stage_bytes() { return (size_t)4 * 32 * 36 * 4; }
-
 int layer_block_cols(int Kp, int elt, int pad) {
-  const size_t stage = layer_stage_bytes();
-  int cap = (int)((kLayerLds - stage) / (32 * (size_t)elt)) - pad;
+  int cap = (int)(kLayerLds / (32 * (size_t)elt)) - pad;
   cap = cap / 32 * 32;
   const int nblk = (Kp + cap - 1) / cap;
   return round_up((Kp + nblk - 1) / nblk, 32);
@@ -1170,25 +977,15 @@ template <typename S>
 hipError_t launch_layer(const LayerArgs<S>& a0, int P, hipStream_t s, const LaunchEv& ev) {
   LayerArgs<S> a = a0;
   a.KB = layer_block_cols(a.Kp, (int)sizeof(S), Op<S>::PAD);
-  const size_t lds = (size_t)32 * (a.KB + Op<S>::PAD) * sizeof(S) + layer_stage_bytes();
+  const size_t lds = (size_t)32 * (a.KB + Op<S>::PAD) * sizeof(S);
   const dim3 grid(a.Np / 32, P);
-  if (a.Bp <= 128 || !a.do_update) {
-    static bool attr = false;
-    if (!attr) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer<S, 128>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLayerLds);
-      attr = true;
-    }
-    hipExtLaunchKernelGGL((k_layer<S, 128>), grid, dim3(256), lds, s, ev.start, ev.stop, 0, a);
-  } else {
-    static bool attr = false;
-    if (!attr) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer<S, 256>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLayerLds);
-      attr = true;
-    }
-    hipExtLaunchKernelGGL((k_layer<S, 256>), grid, dim3(256), lds, s, ev.start, ev.stop, 0, a);
+  static bool attr = false;
+  if (!attr) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer<S>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kLayerLds);
+    attr = true;
   }
+  hipExtLaunchKernelGGL((k_layer<S>), grid, dim3(256), lds, s, ev.start, ev.stop, 0, a);
   return hipGetLastError();
 }
 
@@ -1224,13 +1021,6 @@ hipError_t launch_out(const OutArgs<S>& a, int P, hipStream_t s, const LaunchEv&
     attr = true;
   }
   hipExtLaunchKernelGGL(k_out<S>, grid, dim3(64 * kOutWaves), lds, s, ev.start, ev.stop, 0, a);
-  return hipGetLastError();
-}
-
-template <typename S>
-hipError_t launch_bwd(const BwdArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev) {
-  const int tiles = (a.Kp / 32) * (a.Bp / 32);
-  hipExtLaunchKernelGGL(k_bwd<S>, dim3((tiles + 3) / 4, P), dim3(256), 0, s, ev.start, ev.stop, 0, a);
   return hipGetLastError();
 }
 
@@ -1310,7 +1100,6 @@ hipError_t launch_reduce_partials(const double* part_ce, const unsigned int* par
 template hipError_t launch_layer<uint16_t>(const LayerArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_out<float>(const OutArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_out<uint16_t>(const OutArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
-template hipError_t launch_bwd<uint16_t>(const BwdArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_gather<float>(const GatherArgs&, hipStream_t, const LaunchEv&);
 template hipError_t launch_gather<uint16_t>(const GatherArgs&, hipStream_t, const LaunchEv&);
 template hipError_t launch_transpose<float>(const TransposeArgs&, hipStream_t, const LaunchEv&);

@@ -31,6 +31,7 @@ namespace gevo {
 namespace {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kBlk = 1024;               // values of a block
 constexpr int kTP = 33;                  // row pitch (floats) of a transpose tile in LDS
@@ -61,6 +62,33 @@ template <> struct Blk<float> {
   __host__ __device__ static int off(int r, int l) { return (r >> 2) * 256 + l * 4 + (r & 3); }
 };
 
+template <> struct Blk<uint16_t> {
+  u32x4_t q[2];
+  __device__ __forceinline__ static Blk load(const uint16_t* p, int lane) {
+    Blk b;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) b.q[i] = *reinterpret_cast<const u32x4_t*>(p + i * 512 + lane * 8);
+    return b;
+  }
+  __device__ __forceinline__ static Blk pack(const float (&f)[16]) {
+    uint32_t h[8];
+    to_bf16x2(f, h);
+    Blk b;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b.q[i >> 2][i & 3] = h[i];
+    return b;
+  }
+  __device__ __forceinline__ void store(uint16_t* p, int lane) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4_t*>(p + i * 512 + lane * 8) = q[i];
+  }
+  __device__ __forceinline__ float val(int r) const {
+    const uint32_t h = q[r >> 3][(r >> 1) & 3];
+    return __uint_as_float((r & 1) ? h & 0xffff0000u : h << 16);
+  }
+  __host__ __device__ static int off(int r, int l) { return (r >> 3) * 512 + l * 8 + (r & 7); }
+};
+
 __device__ __forceinline__ f32x16_t blk_mma(const Blk<float>& a, const Blk<float>& b, f32x16_t c) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.q[r >> 2][r & 3], b.q[r >> 2][r & 3], c, 0, 0, 0);
@@ -75,6 +103,22 @@ __device__ __forceinline__ void blk_mma2(const Blk<float>& a0, const Blk<float>&
   for (int r = 0; r < 16; ++r) {
     c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.q[r >> 2][r & 3], b0.q[r >> 2][r & 3], c0, 0, 0, 0);
     c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.q[r >> 2][r & 3], b1.q[r >> 2][r & 3], c1, 0, 0, 0);
+  }
+}
+
+__device__ __forceinline__ f32x16_t mma_bf16(u32x4_t a, u32x4_t b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t blk_mma(const Blk<uint16_t>& a, const Blk<uint16_t>& b, f32x16_t c) {
+  return mma_bf16(a.q[1], b.q[1], mma_bf16(a.q[0], b.q[0], c));
+}
+__device__ __forceinline__ void blk_mma2(const Blk<uint16_t>& a0, const Blk<uint16_t>& b0, f32x16_t& c0,
+                                         const Blk<uint16_t>& a1, const Blk<uint16_t>& b1, f32x16_t& c1) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    c0 = mma_bf16(a0.q[i], b0.q[i], c0);
+    c1 = mma_bf16(a1.q[i], b1.q[i], c1);
   }
 }
 
@@ -859,5 +903,11 @@ template hipError_t launch_tile_pred_out<float>(const TileOutArgs<float>&, int, 
 template hipError_t launch_tile_bwd<float>(const TileBwdArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_tile_fwd<float>(const TileFwdArgs<float>&, int, hipStream_t, const LaunchEv&);
 template hipError_t launch_tile_gather<float>(const GatherArgs&, hipStream_t, const LaunchEv&);
+// bf16: training only
+template hipError_t launch_tile_layer<uint16_t>(const TileLayerArgs<uint16_t>&, int, bool, bool, hipStream_t,
+                                                const LaunchEv&);
+template hipError_t launch_tile_out<uint16_t>(const TileOutArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
+template hipError_t launch_tile_bwd<uint16_t>(const TileBwdArgs<uint16_t>&, int, hipStream_t, const LaunchEv&);
+template hipError_t launch_tile_gather<uint16_t>(const GatherArgs&, hipStream_t, const LaunchEv&);
 
 }  // namespace gevo
