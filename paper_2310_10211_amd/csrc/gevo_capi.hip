@@ -307,6 +307,7 @@ struct gevo_pop {
   Layout y;
   char* ws = nullptr;
   hipStream_t stream = nullptr;
+  int device = 0;           // current at gevo_pop_init
   const float* trX = nullptr;
   const int32_t* trY = nullptr;
   const float* teX = nullptr;
@@ -346,6 +347,18 @@ namespace {
 
 template <typename T>
 T* at(gevo_pop* p, size_t off) { return reinterpret_cast<T*>(p->ws + off); }
+
+// the handle's device, current until the end of the scope
+struct OnDevice {
+  int before = -1;
+  explicit OnDevice(int device) {
+    int d = -1;
+    if (hipGetDevice(&d) == hipSuccess && d != device && hipSetDevice(device) == hipSuccess) before = d;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
 
 constexpr size_t kProfBatch = 4096;   // launches between resolutions of pending timings
 
@@ -1169,6 +1182,7 @@ gevo_status gevo_pop_init(const gevo_pop_config* cfg, void* d_ws, size_t ws_byte
   p->y = y;
   p->ws = reinterpret_cast<char*>(d_ws);
   p->stream = reinterpret_cast<hipStream_t>(hip_stream);
+  (void)hipGetDevice(&p->device);
   p->trX = d_train_x; p->trY = d_train_y; p->teX = d_test_x; p->teY = d_test_y;
   auto fail = [&](gevo_status s) { gevo_pop_destroy(p); return s; };
   {
@@ -1474,6 +1488,7 @@ gevo_status gevo_pop_export(gevo_pop* p, uint32_t v, float* params_out, uint8_t*
   if (!p) return GEVO_E_ARG;
   const Layout& y = p->y;
   if (v >= (uint32_t)y.P) return GEVO_E_ARG;
+  const OnDevice on(p->device);                  // (callers on another device: the copies alone needed none)
   gevo_status stb = sync_masters(p);
   if (stb != GEVO_OK) return stb;
   // The variant in canonical layout on the device, then one copy for the
