@@ -164,8 +164,9 @@ __device__ __forceinline__ void transpose16(float* tile, int lane, const float (
 }  // namespace
 
 // ------------------------------------------------------------ hidden layer
-// Workgroup (NT unit tiles of 32, variant v), four waves, one per SIMD with
-// the whole register file; wave j takes the input blocks j, j + 4, ...  For
+// Workgroup (NT unit tiles of 32, variant v), NW waves: four, one per SIMD with
+// the whole register file, or eight; wave j takes the input blocks j, j + NW,
+// ...  For
 // each block the wave forms, per unit tile,
 //   dW[k][n] = sum_b A[b][k] G[b][n]            (A from the cols image, G from LDS)
 // in accumulator order, applies the masked update to its 16 master values and
@@ -184,27 +185,26 @@ __device__ __forceinline__ void transpose16(float* tile, int lane, const float (
 // kernel that read row-major operands a cache line per lane, one 32-unit tile
 // of whole inputs per workgroup, took 133 us; the MFMAs alone are 43 us, 48
 // with 25 input blocks on four waves.  4 variants of 784-128-10, batch 32:
-// 17 us from 45.
-template <int BT, int NT>
+// 16 us from 45.
+template <int BT, int NT, int NW>
 struct TileLayerLds {
   static constexpr int NTILE = NT * BT;                    // 32 x 32 output tiles
   static constexpr int TR = NTILE < 8 ? NTILE : 8;         // tiles per reduction round
   static constexpr size_t gs = (size_t)NTILE * kBlk * 4;
-  static constexpr size_t red = (size_t)3 * TR * kBlk * 4;
+  static constexpr size_t red = (size_t)(NW - 1) * TR * kBlk * 4;
   static constexpr size_t tiles = gs > red ? gs : red;
   static constexpr size_t bytes = tiles + (size_t)TR * 32 * kTP * 4;
 };
 
-template <typename S, int BT, int NT, bool UPD, bool FWD>
-__global__ __launch_bounds__(256, 1) void k_tile_layer(TileLayerArgs<S> a) {
-  typedef TileLayerLds<BT, NT> Ly;
+template <typename S, int BT, int NT, int NW, bool UPD, bool FWD>
+__global__ __launch_bounds__(64 * NW, 1) void k_tile_layer(TileLayerArgs<S> a) {
+  typedef TileLayerLds<BT, NT, NW> Ly;
   typedef Blk<S> B;
   using O = Op<S>;
-  constexpr int NW = 4;
   extern __shared__ __align__(16) char smem[];
   __shared__ float bias_l[32 * NT];
   S* gs = reinterpret_cast<S*>(smem);                      // [NT][BT] blocks of G (lane = unit, contraction = batch)
-  float* red = reinterpret_cast<float*>(smem);             // after the loop: [3][TR][16][64]
+  float* red = reinterpret_cast<float*>(smem);             // after the loop: [NW - 1][TR][16][64]
   float* tiles = reinterpret_cast<float*>(smem + Ly::tiles);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31;
   const int nt = blockIdx.x * NT, v = blockIdx.y, n0 = nt * 32;
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256, 1) void k_tile_layer(TileLayerArgs<S> a) {
   float* Wv = a.Wm + (size_t)v * a.Np * a.Kp + (size_t)n0 * 32;
   const uint32_t* mk = a.mask + ((size_t)v * a.Np + n0 + l32) * KB;
   const float lrv = UPD ? a.lr[v] : 0.0f;
-  // This wave's blocks are j0, j0 + 4, ... of an order that starts at another
+  // This wave's blocks are j0, j0 + NW, ... of an order that starts at another
   // block in each workgroup of an XCD (workgroup i runs on XCD i % 8), so
   // they do not all ask the L2 for the same lines at once.
   const int j0 = (wave + blockIdx.x + v) % NW, base = (int)((v * gridDim.x + blockIdx.x) >> 3) % KB;
@@ -261,12 +261,13 @@ __global__ __launch_bounds__(256, 1) void k_tile_layer(TileLayerArgs<S> a) {
   if constexpr (UPD) {
     const S* G = a.G + ((size_t)v * NB + nt) * BT * kBlk;
     constexpr int PER = 16 / (int)sizeof(S);
-    for (int i = tid * PER; i < NT * BT * kBlk; i += 256 * PER)
+    for (int i = tid * PER; i < NT * BT * kBlk; i += 64 * NW * PER)
       *reinterpret_cast<uint4*>(gs + i) = *reinterpret_cast<const uint4*>(G + i);
     __syncthreads();
     // bias gradients: eight lanes per unit, fixed-order reduction
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
+      if (tid >= 256) break;
       const int nl = tid >> 3, lh = tid & 1, g = (tid >> 1) & 3;
       float s = 0.0f;
 #pragma unroll
@@ -792,18 +793,25 @@ __global__ __launch_bounds__(256) void k_tile_gather(GatherArgs a) {
 }
 
 // ---------------------------------------------------------------- launchers
-template <typename S, int BT, int NT, bool UPD, bool FWD>
+template <typename S, int BT, int NT, int NW, bool UPD, bool FWD>
 static hipError_t launch_tl(const TileLayerArgs<S>& a, int P, hipStream_t s, const LaunchEv& ev) {
   static bool attr = false;
-  const size_t lds = TileLayerLds<BT, NT>::bytes;
+  const size_t lds = TileLayerLds<BT, NT, NW>::bytes;
   if (!attr) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile_layer<S, BT, NT, UPD, FWD>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile_layer<S, BT, NT, NW, UPD, FWD>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr = true;
   }
-  hipExtLaunchKernelGGL((k_tile_layer<S, BT, NT, UPD, FWD>), dim3(a.Np / 32 / NT, P), dim3(256), lds, s, ev.start,
-                        ev.stop, 0, a);
+  hipExtLaunchKernelGGL((k_tile_layer<S, BT, NT, NW, UPD, FWD>), dim3(a.Np / 32 / NT, P), dim3(64 * NW), lds, s,
+                        ev.start, ev.stop, 0, a);
   return hipGetLastError();
+}
+
+template <typename S, int BT, int NT, int NW>
+static hipError_t launch_tl_uf(const TileLayerArgs<S>& a, int P, bool upd, bool fwd, hipStream_t s, const LaunchEv& ev) {
+  if (upd && fwd) return launch_tl<S, BT, NT, NW, true, true>(a, P, s, ev);
+  if (upd) return launch_tl<S, BT, NT, NW, true, false>(a, P, s, ev);
+  return launch_tl<S, BT, NT, NW, false, true>(a, P, s, ev);
 }
 
 template <typename S, int BT>
@@ -812,14 +820,16 @@ static hipError_t launch_tl_mode(const TileLayerArgs<S>& a, int P, bool upd, boo
   // (eight row tiles of two unit tiles would not fit the registers)
   const int NB = a.Np / 32;
   if constexpr (BT < 8)
-    if (NB % 2 == 0 && (int64_t)P * (NB / 2) >= 256) {
-      if (upd && fwd) return launch_tl<S, BT, 2, true, true>(a, P, s, ev);
-      if (upd) return launch_tl<S, BT, 2, true, false>(a, P, s, ev);
-      return launch_tl<S, BT, 2, false, true>(a, P, s, ev);
-    }
-  if (upd && fwd) return launch_tl<S, BT, 1, true, true>(a, P, s, ev);
-  if (upd) return launch_tl<S, BT, 1, true, false>(a, P, s, ev);
-  return launch_tl<S, BT, 1, false, true>(a, P, s, ev);
+    if (NB % 2 == 0 && (int64_t)P * (NB / 2) >= 256) return launch_tl_uf<S, BT, 2, 4>(a, P, upd, fwd, s, ev);
+  // Eight waves where the chip has a workgroup per CU at most and a wave's
+  // chain of blocks, not the matrix cores, is the time: in bf16 up to 128 rows
+  // (an epoch of 24 variants of 784-300-100-10, batch 100: 2.75 ms with four
+  // waves, 2.66 with eight; 16 of 784-512-10, batch 64: 0.99 and 0.90), in fp32
+  // one row tile (4 of 784-128-10, batch 32: 1.59 and 1.53; with two row tiles,
+  // 16 of 784-300-100-10, 3.56 and 4.04, with four 1.3 and 1.9).
+  if constexpr (BT == 1 || (BT <= 4 && sizeof(S) == 2))
+    if ((int64_t)P * NB <= 256) return launch_tl_uf<S, BT, 1, 8>(a, P, upd, fwd, s, ev);
+  return launch_tl_uf<S, BT, 1, 4>(a, P, upd, fwd, s, ev);
 }
 
 template <typename S>
