@@ -615,7 +615,7 @@ int seg_ps(int channels) { return channels * 2 + 16; }
 
 // LDS bytes of one padded bf16 image in both copies, with room for the 16
 // elements that the last window row's reads run past it (G images: G times)
-int seg_image(int H, int W, int C) { return 2 * (((H + 2) * (W + 2) * C * 2 + 64 + 15) / 16 * 16); }
+int seg_image(int H, int W, int C) { return 2 * ((2 * seg_pitch(H, W, C) + 64 + 15) / 16 * 16); }
 
 // Splits the net into segments whose maps fit a CU's LDS, or leaves nseg = 0.
 // Map j (the output of depthwise layer j) is hin[j + 1] x win[j + 1] x (stem or
@@ -919,7 +919,7 @@ gevo_status cnn_predict_segments(gevo_cnn* h) {
         a.stem_c = y.C;
         a.x = h->teX; a.H = y.H; a.W = y.W;
         a.w2_magic = cnn_magic(y.W + 2);
-        a.pad_magic = cnn_magic((y.H + 2) * (y.W + 2) * y.C);
+        a.pitch_magic = cnn_magic(seg_pitch(y.H, y.W, y.C));
         a.c_magic = cnn_magic(y.C);
         a.im = g.x;
         a.im2 = g.x + g.G * (seg_image(y.H, y.W, y.C) / 2);
@@ -946,7 +946,7 @@ gevo_status cnn_predict_segments(gevo_cnn* h) {
         t.q = (t.Ho + t.parts * halves - 1) / (t.parts * halves);
         t.in = off[at_y];
         t.ps_in = s == 0 ? 0 : seg_ps(chan(s - 1));
-        t.img_in = s == 0 ? (y.H + 2) * (y.W + 2) * y.C * 2 : t.H * t.W * t.ps_in;
+        t.img_in = s == 0 ? 2 * seg_pitch(y.H, y.W, y.C) : t.H * t.W * t.ps_in;
         const bool to_memory = s + 1 == g.s1 && !tail;
         at_y ^= 1;
         t.out = off[at_y];

@@ -12,6 +12,17 @@ constexpr int kSegWaves = 8;                      // waves per workgroup
 constexpr size_t kSegLds = 160 * 1024;            // LDS of a CU
 constexpr int kSegMaxStages = 4;
 
+// The stem's images in LDS: each is (H + 2) x (W + 2) x C bf16 elements with a
+// zero border, padded to an even count, so that every image of a group begins
+// on a dword whatever H, W and C are (with 7x7x1 or 15x15x3 back to back, every
+// second image's windows would be read through misaligned dwords).
+constexpr int seg_pitch(int H, int W, int C) { return ((H + 2) * (W + 2) * C + 1) / 2 * 2; }   // elements
+
+// A window row starts at any element e of its image and is read in dwords: at
+// even e from the images at byte im, at odd e from their copy at im2, which lies
+// one element further on.  (Bytes from the image's first; e >= 0.)
+constexpr int seg_window(int im, int im2, int e) { return ((e & 1) ? im2 : im) + 4 * ((e + 1) >> 1); }
+
 // A producing layer (the stem, or a pointwise layer) and the depthwise layer
 // after it, from one map in LDS to the next (LDS or, for the segment's last
 // stage without a tail, global memory).
@@ -35,7 +46,7 @@ struct CnnSegArgs {
   // source: the images (stem_c > 0) or a map [v][image][pixels][channels] in global memory
   int stem_c;                                     // input channels of the stem, 0: no stem
   const float* x; int64_t img0, n_test; int H, W; // images; first of the launch, one past its last
-  uint32_t w2_magic, pad_magic, c_magic;          // ceil(2^32 / d) for d = W + 2, (H + 2) (W + 2) C, C
+  uint32_t w2_magic, pitch_magic, c_magic;        // ceil(2^32 / d) for d = W + 2, seg_pitch(H, W, C), C
   int im, im2;                                    // LDS byte offsets of the padded bf16 images and their copy
                                                   // one element further on
   const uint16_t* src; size_t src_vs;             // source map, elements per variant

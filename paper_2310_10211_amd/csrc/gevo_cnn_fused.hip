@@ -232,7 +232,7 @@ __device__ __forceinline__ void stage_run(const CnnSegArgs& a, const CnnSegStage
           int e = (yc * (W + 2) + axc) * a.stem_c;
 #pragma unroll
           for (int s = 0; s < NS; ++s, e += (W + 2) * a.stem_c) {
-            const uint32_t* im = reinterpret_cast<const uint32_t*>(src + ((e & 1) ? a.im2 : a.im)) + ((e + 1) >> 1) + 4 * lh;
+            const uint32_t* im = reinterpret_cast<const uint32_t*>(src + seg_window(a.im, a.im2, e)) + 4 * lh;
 #pragma unroll
             for (int j = 0; j < 4; ++j) op[s][j] = im[j];
           }
@@ -455,11 +455,11 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void k_cnn_seg(CnnSegArgs) {
   // of them by thread i % 512: read into registers (small images: during the
   // previous group's first stage), then written.
   constexpr int kPre = 8;
-  const int W2 = a.W + 2, pad1 = (a.H + 2) * W2 * a.stem_c, npad = a.stem_c ? pad1 * a.G : 0;
+  const int W2 = a.W + 2, pitch = seg_pitch(a.H, a.W, a.stem_c), npad = a.stem_c ? pitch * a.G : 0;
   const bool ahead = npad <= kPre * 64 * kSegWaves;
   float pre[kPre];
   auto source = [&](int i) {                       // element i's place from the group's first pixel, ~0: border
-    const int im = (int)__umulhi((uint32_t)i, a.pad_magic), e = i - im * pad1;
+    const int im = (int)__umulhi((uint32_t)i, a.pitch_magic), e = i - im * pitch;   // (the padding is a border)
     const int pix = a.stem_c == 1 ? e : (int)__umulhi((uint32_t)e, a.c_magic);   // (the magic of 1 does not fit)
     const int py = (int)__umulhi((uint32_t)pix, a.w2_magic), yy = py - 1, xx = pix - py * W2 - 1;
     return i < npad && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W

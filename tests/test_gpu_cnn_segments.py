@@ -24,6 +24,9 @@ SHAPES = [
     (12, 12, 3, 32, [(1, 128)], 9, 3),                           # pooled map of 144
     (8, 4, 3, 32, [(2, 128)], 21, 3),                            # pooled map of 8
     (4, 4, 1, 32, [(1, 128)], 19, 3),                            # pooled map of 16, narrow rows
+    (7, 7, 3, 32, [(2, 128)], 11, 3),                            # odd images back to back: an odd element count each
+    (15, 15, 1, 64, [(2, 128), (1, 128)], 19, 3),
+    (31, 31, 3, 32, [(2, 128), (2, 128)], 6, 2),
     (4, 4, 3, 32, [(2, 128), (1, 128)], 4170, 9),                # pooled map of 4; two launches, two groups a workgroup
 ]
 
