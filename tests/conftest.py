@@ -30,3 +30,22 @@ def read_golden(name):
 @pytest.fixture
 def golden():
     return read_golden
+
+
+def training_path(pop, train):
+    """Runs train(), the first training of a new population, and names the
+    kernels that it ran on, from the launches that the library counts: "fused"
+    (whole steps in one launch), "streamed n" (n hidden layers on the streaming
+    kernel, which has two launches for each layer's register image and mask
+    words made first) or "tiles"."""
+    pop.set_profiling(True)
+    before = pop.kernel_stats()
+    train()
+    after = pop.kernel_stats()
+    pop.set_profiling(False)
+    n = {k: after[k][1] - before[k][1] for k in after}
+    if n["fused_train"]:
+        return "fused"
+    assert n["layer_train"] > 0
+    images = n["aux"] - 1                                # beside the launch that clears the epoch's sums
+    return "streamed %d" % (images // 2) if images else "tiles"

@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 import synthetic
+from conftest import training_path
 
 pytestmark = pytest.mark.gpu
 
@@ -172,31 +173,38 @@ def test_config1_full_fp32():
     pop.close()
 
 
-def test_bf16_two_layer_ragged_batch():
+@pytest.mark.parametrize("P,path", [(8, "tiles"), (36, "fused")])
+def test_bf16_two_layer_ragged_batch(P, path):
     """784-256-10 bf16 (config 3 shape), 4,100 train rows -> last batch of 4, 2 epochs."""
-    cfg, data = _small(3, P=8, n_train=4100, n_test=1000, epochs=2)
+    cfg, data = _small(3, P=P, n_train=4100, n_test=1000, epochs=2)
     pop = _pop(cfg, data)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     pop.train_epoch(1)
     pop.predict()
     s = pop.scores()
-    ref = oracle.evaluate(cfg, data, epochs=2)
-    _check_losses(s, ref, range(8), BF16_LOSS_RTOL)
+    sample = list(range(7)) + [P - 1]
+    ref = oracle.evaluate(cfg, data, variants=sample, epochs=2)
+    _check_losses(s, ref, sample, BF16_LOSS_RTOL)
     pop.close()
 
 
-@pytest.mark.parametrize("dims,batch,n_train", [
-    ([784, 128, 10], 32, 700),      # hidden 128, batch tile 32, ragged tail
-    ([784, 100, 10], 64, 650),      # hidden 100 (padded to 128), batch tile 64
-    ([784, 128, 10], 128, 600),     # hidden 128, batch tile 128
-    ([784, 256, 10], 50, 620),      # hidden 256, batch 50 (tile 64)
-    ([300, 250, 7], 20, 500),       # input 300 (10 column blocks), hidden 250, 7 classes, tile 32
-    ([784, 256, 16], 128, 600),     # 16 classes: the largest count of the 16-row logits tiles
-    ([784, 128, 24], 64, 600),      # 24 classes: 32-row logits tiles
+@pytest.mark.parametrize("dims,batch,n_train,P,path", [
+    ([784, 128, 10], 32, 700, 3, "fused"),      # hidden 128, batch tile 32, ragged tail
+    ([784, 100, 10], 64, 650, 3, "fused"),      # hidden 100 (padded to 128), batch tile 64
+    ([784, 128, 10], 128, 600, 65, "fused"),    # hidden 128, batch tile 128
+    ([784, 128, 10], 128, 600, 64, "tiles"),
+    ([784, 256, 10], 50, 620, 3, "fused"),      # hidden 256, batch 50 (tile 64)
+    ([300, 250, 7], 20, 500, 3, "fused"),       # input 300 (10 column blocks), hidden 250, 7 classes, tile 32
+    ([480, 256, 10], 128, 600, 3, "fused"),     # batch tile 128 with few inputs
+    ([784, 256, 16], 128, 600, 33, "fused"),    # 16 classes: the largest count of the 16-row logits tiles
+    ([784, 256, 16], 128, 600, 32, "tiles"),
+    ([784, 128, 24], 64, 600, 3, "fused"),      # 24 classes: 32-row logits tiles
+    ([784, 128, 24], 128, 600, 65, "fused"),
 ])
-def test_bf16_two_layer_shapes(dims, batch, n_train):
-    """Two-layer bf16 nets at the other hidden widths and batch tiles of the per-variant training kernel."""
-    cfg, data = _small(3, P=3, n_train=n_train, n_test=300, dims=dims, batch=batch)
+def test_bf16_two_layer_shapes(dims, batch, n_train, P, path):
+    """Two-layer bf16 nets at the other hidden widths and batch tiles of the
+    per-variant training kernel, and on the tile kernels where the population is small."""
+    cfg, data = _small(3, P=P, n_train=n_train, n_test=300, dims=dims, batch=batch)
     if dims[0] != 784:
         data["x_train"] = data["x_train"][:, :dims[0]].copy()
         data["x_test"] = data["x_test"][:, :dims[0]].copy()
@@ -205,33 +213,36 @@ def test_bf16_two_layer_shapes(dims, batch, n_train):
             y = data[split]
             data[split] = ((y + 10 * (np.arange(len(y)) % 3)) % dims[-1]).astype(y.dtype)
     pop = _pop(cfg, data)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     pop.predict()
     s = pop.scores()
-    ref = oracle.evaluate(cfg, data, epochs=1)
-    _check_losses(s, ref, range(3), BF16_LOSS_RTOL)
+    sample = sorted({0, 1, P - 1})
+    ref = oracle.evaluate(cfg, data, variants=sample, epochs=1)
+    _check_losses(s, ref, sample, BF16_LOSS_RTOL)
     pop.close()
 
 
-@pytest.mark.parametrize("i,dims,batch", [
-    (3, None, None),
-    (5, [1024, 256, 128, 10], 256),      # hidden layers on the streaming kernel's register-image masters
+@pytest.mark.parametrize("i,dims,batch,P,path", [
+    (3, None, None, 33, "fused"),
+    (3, None, None, 3, "tiles"),
+    (5, [1024, 256, 128, 10], 256, 33, "streamed 2"),    # hidden layers on the streaming kernel's register-image masters
+    (5, [1024, 256, 128, 10], 256, 3, "tiles"),
 ])
-def test_export_import_round_trip_between_epochs_is_exact(i, dims, batch):
+def test_export_import_round_trip_between_epochs_is_exact(i, dims, batch, P, path):
     """Exporting and re-importing every variant between epochs (the register-image
     copies of the fused two-layer kernel and of the streamed hidden layers are
     rebuilt from the imported master) leaves the run bitwise unchanged."""
     over = {"epochs": 2}
     if dims:
         over.update(dims=dims, batch=batch)
-    cfg, data = _small(i, P=3, n_train=700, n_test=256, **over)
+    cfg, data = _small(i, P=P, n_train=700, n_test=256, **over)
     if dims and dims[0] != 3072:
         data["x_train"] = data["x_train"][:, :dims[0]].copy()
         data["x_test"] = data["x_test"][:, :dims[0]].copy()
     runs = []
     for round_trip in (False, True):
         pop = _pop(cfg, data)
-        pop.train_epoch(0)
+        assert training_path(pop, lambda: pop.train_epoch(0)) == path
         if round_trip:
             for v in range(cfg["P"]):
                 pop.import_params(v, pop.export(v)["params"])
@@ -242,22 +253,24 @@ def test_export_import_round_trip_between_epochs_is_exact(i, dims, batch):
     assert not differing, f"variants whose parameters differ: {differing}"
 
 
-def test_bf16_one_step_after_import_matches_oracle():
+@pytest.mark.parametrize("P,path", [(2, "tiles"), (33, "fused")])
+def test_bf16_one_step_after_import_matches_oracle(P, path):
     """An imported state trains from that state: one bf16 SGD step of the
     784-256-10 net against the oracle from the same state."""
-    cfg, data = _small(3, P=2, n_train=256, n_test=256)
+    cfg, data = _small(3, P=P, n_train=256, n_test=256)
     dims = cfg["dims"]
     pop = _pop(cfg, data)
-    ref = oracle.population(cfg)
+    sample = [0, P - 1]
+    ref = oracle.population(cfg, sample)
     rng = np.random.default_rng(5)
     perm = oracle.permutation(cfg["seed"], 0, 256)
-    for v in range(cfg["P"]):
+    for v in sample:
         st = ref[v]
         p = st["params"] + 0.01 * rng.standard_normal(st["params"].shape)
         pop.import_params(v, p.astype(np.float32))             # masked weights are imported as +0
         st["params"] = pop.export(v)["params"].astype(np.float64)
-    pop.train_steps(0, 0, 1)
-    for v in range(cfg["P"]):
+    assert training_path(pop, lambda: pop.train_steps(0, 0, 1)) == path
+    for v in sample:
         st = ref[v]
         q = st["params"].copy()
         oracle.train_steps("bf16", dims, q, st["mask"], st["lr"], data["x_train"], data["y_train"], perm,
@@ -281,28 +294,31 @@ def test_bf16_three_layer():
     pop.close()
 
 
-@pytest.mark.parametrize("dims,batch,n_train", [
-    ([3072, 256, 128, 10], 256, 1300),    # both hidden layers on the streaming kernel, ragged tail of 20
-    ([512, 128, 256, 10], 100, 730),      # batch tile 128
-    ([3072, 192, 128, 10], 256, 800),     # first hidden layer on the blocked kernel (192 units), second streamed
-    ([3072, 256, 160, 10], 256, 700),     # second layer's 256 inputs streamed, 160 units on the blocked kernel
-    ([1024, 384, 256, 10], 128, 700),     # three 128-unit tiles per variant, batch tile 128
+@pytest.mark.parametrize("dims,batch,n_train,P,path", [
+    ([3072, 256, 128, 10], 256, 1300, 33, "streamed 2"),   # both hidden layers on the streaming kernel, ragged tail of 20
+    ([3072, 256, 128, 10], 256, 1300, 3, "tiles"),
+    ([512, 128, 256, 10], 100, 730, 33, "streamed 2"),     # batch tile 128
+    ([512, 128, 256, 10], 100, 730, 3, "tiles"),
+    ([3072, 192, 128, 10], 256, 800, 65, "tiles"),         # the first hidden layer (192 units) has no streaming width
+    ([3072, 256, 160, 10], 256, 700, 3, "tiles"),
+    ([1024, 384, 256, 10], 128, 700, 22, "streamed 2"),    # three 128-unit tiles per variant, batch tile 128
+    ([1024, 384, 256, 10], 128, 700, 3, "tiles"),
 ])
-def test_bf16_deep_nets_on_the_streaming_layer_kernel(dims, batch, n_train):
+def test_bf16_deep_nets_on_the_streaming_layer_kernel(dims, batch, n_train, P, path):
     """Hidden layers whose widths are multiples of 128 and whose inputs are
     multiples of 64, at batch tiles 128 and 256, train through the streaming
-    hidden-layer kernel; the other layers of the same nets through the
-    blocked one."""
-    cfg, data = _small(5, P=3, n_train=n_train, n_test=400, dims=dims, batch=batch)
+    hidden-layer kernel; other nets and small populations on the tile kernels."""
+    cfg, data = _small(5, P=P, n_train=n_train, n_test=400, dims=dims, batch=batch)
     if dims[0] != 3072:
         data["x_train"] = data["x_train"][:, :dims[0]].copy()
         data["x_test"] = data["x_test"][:, :dims[0]].copy()
     pop = _pop(cfg, data)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     pop.predict()
     s = pop.scores()
-    ref = oracle.evaluate(cfg, data, epochs=1)
-    _check_losses(s, ref, range(3), BF16_LOSS_RTOL)
+    sample = sorted({0, 1, P - 1})
+    ref = oracle.evaluate(cfg, data, variants=sample, epochs=1)
+    _check_losses(s, ref, sample, BF16_LOSS_RTOL)
     pop.close()
 
 
@@ -340,23 +356,25 @@ def test_single_layer_net():
 
 
 # --------------------------------------------------------------- invariants
-def test_lr_zero_leaves_weights_bitwise_unchanged():
-    cfg, data = _small(3, P=3, n_train=512, n_test=256, lr=(0.0, 0.0))
+@pytest.mark.parametrize("P,path", [(3, "tiles"), (33, "fused")])
+def test_lr_zero_leaves_weights_bitwise_unchanged(P, path):
+    cfg, data = _small(3, P=P, n_train=512, n_test=256, lr=(0.0, 0.0))
     pop = _pop(cfg, data)
-    before = [pop.export(v)["params"] for v in range(3)]
-    pop.train_epoch(0)
-    for v in range(3):
+    before = [pop.export(v)["params"] for v in range(P)]
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
+    for v in range(P):
         assert pop.export(v)["params"].tobytes() == before[v].tobytes()
     pop.close()
 
 
-def test_masked_weights_stay_plus_zero_and_divergence_is_contained():
-    cfg, data = _small(3, P=12, n_train=1024, n_test=256, lr=(1e-2, 1e4), dens=(0.3, 0.6))
+@pytest.mark.parametrize("P,path", [(12, "tiles"), (36, "fused")])
+def test_masked_weights_stay_plus_zero_and_divergence_is_contained(P, path):
+    cfg, data = _small(3, P=P, n_train=1024, n_test=256, lr=(1e-2, 1e4), dens=(0.3, 0.6))
     pop = _pop(cfg, data)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     pop.predict()
     s = pop.scores()
-    ref = oracle.evaluate(cfg, data, epochs=1)
+    ref = oracle.evaluate(cfg, data, variants=list(range(12)), epochs=1)
     healthy = [v for v in range(12) if ref[v]["lr"] < 0.3]
     assert healthy and len(healthy) < 12
     _check_losses(s, ref, healthy, BF16_LOSS_RTOL)
@@ -385,15 +403,16 @@ def test_variants_are_independent_of_population_size():
     a.close(); b.close()
 
 
-def test_runs_are_deterministic_and_steps_compose():
-    cfg, data = _small(3, P=4, n_train=1000, n_test=256)
+@pytest.mark.parametrize("P,path", [(4, "tiles"), (33, "fused")])
+def test_runs_are_deterministic_and_steps_compose(P, path):
+    cfg, data = _small(3, P=P, n_train=1000, n_test=256)
     a = _pop(cfg, data)
-    a.train_epoch(0)
+    assert training_path(a, lambda: a.train_epoch(0)) == path
     b = _pop(cfg, data)
     T = b.steps_per_epoch
     b.train_steps(0, 0, 3)
     b.train_steps(0, 3, T)
-    for v in range(4):
+    for v in range(P):
         assert a.export(v)["params"].tobytes() == b.export(v)["params"].tobytes()
     assert a.scores()["train_loss"].tobytes() == b.scores()["train_loss"].tobytes()
     a.close(); b.close()

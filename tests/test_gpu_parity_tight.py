@@ -2,10 +2,14 @@
 per-sample prediction, and the argmax tie and NaN-logit rules on the GPU.
 
 * One SGD step from an imported state, weight and bias updates element by
-  element against the oracle in bf16 mode (bounds derived in _check_update), for nets whose hidden layers train in the
-  streaming kernel (with the backward GEMM and the output kernel), including
-  the full 3072-1024-512-10 width, and for the fused two-layer kernel at
-  variants whose column blocks are visited in rotated order.
+  element against the oracle in bf16 mode (bounds derived in _check_update), on
+  each training path and on both sides of the population sizes that divide them:
+  nets whose hidden layers train in the streaming kernel (with the backward GEMM
+  and the output kernel), including the full 3072-1024-512-10 width, nets whose
+  first layer does and whose second trains beside it, the same nets with fewer
+  variants on the tile kernels, and the fused two-layer kernel at variants whose
+  column blocks are visited in rotated order.  Each case names the kernels that
+  have to have run.
 * Prediction of single rows (each variant's test loss is then one sample's
   cross-entropy) on the 784-512-256-10 net of the prediction workload, and a
   ragged three-tile test set against the oracle's per-row logits.
@@ -20,6 +24,7 @@ import pytest
 
 import oracle
 import synthetic
+from conftest import training_path
 
 pytestmark = pytest.mark.gpu
 
@@ -81,7 +86,7 @@ def _compare_step(got, want, before, dims, what):
         _check_update(bg - b0, br - b0, f"{what} layer {l + 1} biases")
 
 
-def _one_step_case(cfg, data, variants, seed=5):
+def _one_step_case(cfg, data, variants, path, seed=5):
     dims = cfg["dims"]
     pop = _pop(cfg, data)
     ref = oracle.population(cfg, variants)
@@ -93,7 +98,7 @@ def _one_step_case(cfg, data, variants, seed=5):
         p = st["params"] + 0.01 * rng.standard_normal(st["params"].shape)
         pop.import_params(v, p.astype(np.float32))            # masked weights are imported as +0
         before[v] = pop.export(v)["params"].astype(np.float64)
-    pop.train_steps(0, 0, 1)
+    assert training_path(pop, lambda: pop.train_steps(0, 0, 1)) == path
     got = {v: pop.export(v)["params"].astype(np.float64) for v in variants}
     pop.close()
     for v in variants:
@@ -104,21 +109,27 @@ def _one_step_case(cfg, data, variants, seed=5):
         _compare_step(got[v], q, before[v], dims, f"variant {v}")
 
 
-@pytest.mark.parametrize("dims,batch,n_train,P", [
-    ([1024, 256, 128, 10], 256, 700, 3),     # both hidden layers streamed, batch tile 256
-    ([512, 128, 256, 10], 128, 300, 3),      # batch tile 128
-    ([3072, 1024, 512, 10], 256, 512, 2),    # the full width of the 128-variant CIFAR-shaped workload
+@pytest.mark.parametrize("dims,batch,n_train,P,path", [
+    ([1024, 256, 128, 10], 256, 700, 33, "streamed 2"),     # both hidden layers streamed, batch tile 256
+    ([1024, 256, 128, 10], 256, 700, 32, "tiles"),
+    ([512, 128, 256, 10], 128, 300, 33, "streamed 2"),      # batch tile 128
+    ([512, 128, 256, 10], 128, 300, 3, "tiles"),
+    ([512, 128, 10], 250, 300, 65, "streamed 1"),           # one hidden layer, no backward GEMM
+    ([3072, 1024, 512, 10], 256, 512, 9, "streamed 2"),     # the full width of the 128-variant CIFAR-shaped workload
+    ([3072, 1024, 512, 10], 256, 512, 2, "tiles"),
 ])
-def test_streamed_net_one_step_elementwise(dims, batch, n_train, P):
+def test_streamed_net_one_step_elementwise(dims, batch, n_train, P, path):
     cfg = synthetic.config(5, P=P, dims=dims, batch=batch, lr=(0.05, 0.05))
     data = _data(5, n_train, 256, dims)
-    _one_step_case(cfg, data, list(range(P)))
+    _one_step_case(cfg, data, sorted({0, 1, P - 1}), path)
 
 
 # The 784-256-10 bf16 nets with a 128-row batch train in the streaming fused
-# kernel; GEVO_RESIDENT=1 selects the resident kernel (a pair of workgroups
-# per variant) for the same shapes.
+# kernel from 33 variants up and on the tile kernels below; GEVO_RESIDENT=1
+# selects the resident kernel (a pair of workgroups per variant) for the same
+# shapes.
 KERNELS = ["resident", "streaming"]
+RUNS = [("resident", 24, "fused"), ("streaming", 24, "tiles"), ("streaming", 40, "fused")]
 
 
 def _select_kernel(monkeypatch, kernel):
@@ -128,24 +139,24 @@ def _select_kernel(monkeypatch, kernel):
         monkeypatch.delenv("GEVO_RESIDENT", raising=False)
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-def test_fused_kernel_rotated_block_order_one_step_elementwise(kernel, monkeypatch):
+@pytest.mark.parametrize("kernel,P,path", RUNS)
+def test_fused_kernel_rotated_block_order_one_step_elementwise(kernel, P, path, monkeypatch):
     """Variant v of the streaming fused kernel visits its column blocks from
-    block (v / 8) mod 25: variants 8 and 23 start at blocks 1 and 2.  In the
+    block (v / 8) mod 25: variants 8, 23 and 39 start at blocks 1, 2 and 4.  In the
     resident kernel variants 16 and 23 are the second pairs of their XCDs."""
     _select_kernel(monkeypatch, kernel)
-    cfg = synthetic.config(3, P=24, lr=(0.05, 0.2))
+    cfg = synthetic.config(3, P=P, lr=(0.05, 0.2))
     data = _data(3, 256, 256, cfg["dims"])
-    _one_step_case(cfg, data, [0, 8, 16, 23])
+    _one_step_case(cfg, data, [0, 8, 16, 23] + ([39] if P > 24 else []), path)
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-def test_fused_kernel_rotated_block_order_epoch(kernel, monkeypatch):
+@pytest.mark.parametrize("kernel,P,path", RUNS)
+def test_fused_kernel_rotated_block_order_epoch(kernel, P, path, monkeypatch):
     _select_kernel(monkeypatch, kernel)
-    cfg = synthetic.config(3, P=24)
+    cfg = synthetic.config(3, P=P)
     data = _data(3, 700, 300, cfg["dims"])
     pop = _pop(cfg, data)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     pop.predict()
     s = pop.scores()
     pop.close()
@@ -157,18 +168,20 @@ def test_fused_kernel_rotated_block_order_epoch(kernel, monkeypatch):
         assert abs(float(s["train_acc"][v]) - r["train_acc"][-1]) <= 0.005, v
 
 
-def test_resident_and_streaming_fused_kernels_agree(monkeypatch):
-    """The two two-layer training kernels on one population (a ragged last
-    batch of 20 rows, more variants than one dispatch round of pairs would
-    need on a small grid): per-variant scores and the trained weights agree
-    to the bf16 rounding of their different fp32 summation orders."""
-    cfg = synthetic.config(3, P=20)
+@pytest.mark.parametrize("P,path", [(20, "tiles"), (36, "fused")])
+def test_resident_and_streaming_fused_kernels_agree(P, path, monkeypatch):
+    """The resident kernel and the one that the population otherwise trains in,
+    on one population (a ragged last batch of 20 rows, more variants than one
+    dispatch round of pairs would need on a small grid): per-variant scores and
+    the trained weights agree to the bf16 rounding of their different fp32
+    summation orders."""
+    cfg = synthetic.config(3, P=P)
     data = _data(3, 1300, 300, cfg["dims"])
     out = {}
     for kernel in KERNELS:
         _select_kernel(monkeypatch, kernel)
         pop = _pop(cfg, data)
-        pop.train_epoch(0)
+        assert training_path(pop, lambda: pop.train_epoch(0)) == ("fused" if kernel == "resident" else path)
         pop.predict()
         out[kernel] = (pop.scores(), [pop.export(v)["params"] for v in range(cfg["P"])])
         pop.close()
@@ -295,22 +308,25 @@ def test_prediction_argmax_ties_and_nan_logits(i, dims):
             assert float(s["test_loss"][v]) == pytest.approx(ce, rel=1e-5), (v, s["test_loss"][v], ce)
 
 
-@pytest.mark.parametrize("i,dims,batch", [
-    (3, [784, 256, 10], 128),           # fused two-layer kernel
-    (5, [1024, 256, 128, 10], 256),     # streaming, backward GEMM and output kernels
-    (2, [784, 96, 10], 64),             # fp32 output kernel
+@pytest.mark.parametrize("i,dims,batch,P,path", [
+    (3, [784, 256, 10], 128, 33, "fused"),
+    (3, [784, 256, 10], 128, 4, "tiles"),
+    (3, [784, 256, 10], 64, 4, "fused"),                    # batch tile 64
+    (5, [1024, 256, 128, 10], 256, 33, "streamed 2"),       # streaming, backward GEMM and output kernels
+    (5, [1024, 256, 128, 10], 256, 4, "tiles"),
+    (2, [784, 96, 10], 64, 4, "tiles"),                     # fp32
 ])
-def test_training_argmax_ties_and_nan_logits(i, dims, batch):
+def test_training_argmax_ties_and_nan_logits(i, dims, batch, P, path):
     """Learning rate 0: the training-split accuracy and loss of an epoch are
     the same closed forms over the training labels; a NaN logit leaves its
     variant at accuracy 0 and NaN loss and the other variants untouched."""
-    cfg = synthetic.config(i, P=4, dims=dims, batch=batch, lr=(0.0, 0.0), dens=(1.0, 1.0))
+    cfg = synthetic.config(i, P=P, dims=dims, batch=batch, lr=(0.0, 0.0), dens=(1.0, 1.0))
     cfg.pop("dens_list", None)
     data = _data(i, 500, 256, dims)
     pop = _pop(cfg, data)
     for v, b in enumerate(_BIASES):
         pop.import_params(v, _tie_params(dims, b))
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     s = pop.scores()
     pop.close()
     for v, b in enumerate(_BIASES):

@@ -6,6 +6,7 @@ import pytest
 
 import oracle
 import synthetic
+from conftest import training_path
 from oracle import nsga2 as ns
 
 pytestmark = pytest.mark.gpu
@@ -78,14 +79,15 @@ def test_single_edit_genome_reproduces_the_initial_population():
     pop.close()
 
 
-@pytest.mark.parametrize("i,mode,rtol", [(1, "f32", 1e-4), (3, "bf16", 2e-2)])
-def test_training_after_set_genomes_matches_oracle(i, mode, rtol):
+@pytest.mark.parametrize("i,mode,rtol,P,path", [(1, "f32", 1e-4, 4, "tiles"), (3, "bf16", 2e-2, 33, "fused"),
+                                                (3, "bf16", 2e-2, 4, "tiles")])
+def test_training_after_set_genomes_matches_oracle(i, mode, rtol, P, path):
     """One epoch after a rebuild (the fused bf16 kernel must pick up the new
     hidden layer) against the oracle's SGD on the same masks and rates."""
-    cfg, data = _small(i, P=4, n_train=640, n_test=256)
+    cfg, data = _small(i, P=P, n_train=640, n_test=256)
     pop = _pop(cfg, data)
-    pop.train_epoch(0)                                         # the old population trains first
-    genomes = _genomes(4, 47)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path   # the old population trains first
+    genomes = _genomes(P, 47)
     lr, _ = pop.set_genomes(genomes, 0.05)
     pop.train_epoch(0)
     s = pop.scores()
@@ -140,6 +142,7 @@ def test_search_generations_are_deterministic_and_keep_elites():
 
 
 def _struct_genomes(P, dims, seed):
+    """The first four variants carry one structural edit of each kind."""
     gs = ns.initial(P, seed, 0.4, 3, 0, 0.6, dims)
     L = len(dims) - 1
     gs[0] = [(ns.BIAS_EDIT, L, 0)]                              # output biases removed
@@ -179,10 +182,15 @@ def _struct_reference(cfg, genome, lr_base):
     return lr, mask, bmask, params, frozen
 
 
-@pytest.mark.parametrize("i,dims", [(1, None), (3, None), (3, [200, 96, 64, 10]),
-                                    (5, [1024, 256, 128, 10])])   # a removed 128-unit tile of the streaming kernel
-def test_structural_genomes_rebuild_and_train_like_the_oracle(i, dims):
-    cfg, data = _small(i, P=4, n_train=640, n_test=256)
+@pytest.mark.parametrize("i,dims,P,path", [
+    (1, None, 4, "tiles"), (3, None, 33, "fused"), (3, None, 4, "tiles"), (3, [200, 96, 64, 10], 4, "tiles"),
+    (1, [200, 128, 64, 10], 128, "tiles"),                     # fp32, two unit tiles a workgroup: skipped pairs
+    (3, [200, 128, 64, 10], 128, "tiles"),                     # and in bf16
+    (5, [1024, 256, 128, 10], 33, "streamed 2"),               # a removed 128-unit tile of the streaming kernel
+    (5, [1024, 256, 128, 10], 4, "tiles"),
+])
+def test_structural_genomes_rebuild_and_train_like_the_oracle(i, dims, P, path):
+    cfg, data = _small(i, P=P, n_train=640, n_test=256)
     if dims:
         cfg["dims"] = dims
         for k in ("x_train", "x_test"):
@@ -190,7 +198,7 @@ def test_structural_genomes_rebuild_and_train_like_the_oracle(i, dims):
     mode = "bf16" if cfg["dtype"] == "bf16" else "f32"
     rtol = 2e-2 if mode == "bf16" else 1e-4
     pop = _pop(cfg, data)
-    genomes = _struct_genomes(4, cfg["dims"], 61)
+    genomes = _struct_genomes(P, cfg["dims"], 61)
     lr, dens = pop.set_genomes(genomes, 0.05)
     refs = [_struct_reference(cfg, genomes[v], 0.05) for v in range(4)]
     for v in range(4):
@@ -199,7 +207,7 @@ def test_structural_genomes_rebuild_and_train_like_the_oracle(i, dims):
         assert np.array_equal(e["mask"], r_mask), v
         assert np.array_equal(e["params"].astype(np.float64), r_params), v
         assert lr[v] == np.float32(r_lr) and dens[v] == ns.density(genomes[v], cfg["dims"])
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     s = pop.scores()
     n = len(data["y_train"])
     perm = oracle.permutation(cfg["seed"], 0, n)
@@ -241,20 +249,22 @@ def test_time_s_splits_the_call_time_over_the_variants():
     pop.close()
 
 
-def test_narrowed_variants_measure_less_device_time():
-    """3072-1024-512-10 in bf16: variants 4..7 keep 128 units of each hidden
-    layer, so 7 of 8 and 3 of 4 unit tiles of their streaming-kernel
-    workgroups are skipped; their share of the epoch's time is well below
-    that of the full variants 0..3, and they still train like the oracle's
-    narrowed nets (checked by the structural-genome test above)."""
-    cfg, data = _small(5, P=8, n_train=1024, n_test=256)
+@pytest.mark.parametrize("P,path", [(10, "streamed 2"), (8, "tiles")])
+def test_narrowed_variants_measure_less_device_time(P, path):
+    """3072-1024-512-10 in bf16: the second half of the variants keep 128 units
+    of each hidden layer, so 7 of 8 and 3 of 4 of their streaming-kernel
+    workgroups (28 of 32 and 12 of 16 of the tile kernel's) are skipped; their
+    share of the epoch's time is well below that of the full variants, and they
+    still train like the oracle's narrowed nets (checked by the
+    structural-genome test above)."""
+    cfg, data = _small(5, P=P, n_train=1024, n_test=256)
     pop = _pop(cfg, data)
     full = [(ns.LR_EDIT, 0, ns._f32_bits(1.0))]
     narrow = full + [(ns.WIDTH_EDIT, 1, 128), (ns.WIDTH_EDIT, 2, 128)]
-    pop.set_genomes([full] * 4 + [narrow] * 4, 0.01)
-    pop.train_epoch(0)
+    pop.set_genomes([full] * (P // 2) + [narrow] * (P // 2), 0.01)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     t = pop.scores()["time_s"]
-    assert np.max(t[4:]) < 0.6 * np.min(t[:4]), t
+    assert np.max(t[P // 2:]) < 0.6 * np.min(t[:P // 2]), t
     pop.close()
 
 

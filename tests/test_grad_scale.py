@@ -6,6 +6,7 @@ import pytest
 
 import oracle
 import synthetic
+from conftest import training_path
 
 DIMS = [12, 7, 5, 4]
 
@@ -109,15 +110,18 @@ def _paper_like(B, C, seed, P):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("i,dims,mode,rtol", [
-    (1, None, "f32", 1e-4),                       # output kernel, fp32
-    (3, None, "bf16", 2e-2),                      # fused kernel, up to 16 classes
-    (3, [784, 128, 24], "bf16", 2e-2),            # fused kernel, 32-row logits tiles
-    (3, [200, 96, 64, 10], "bf16", 2e-2),         # three layers: output kernel, bf16
+@pytest.mark.parametrize("i,dims,mode,rtol,P,path", [
+    (1, None, "f32", 1e-4, 4, "tiles"),
+    (3, None, "bf16", 2e-2, 33, "fused"),                      # fused kernel, up to 16 classes
+    (3, None, "bf16", 2e-2, 4, "tiles"),
+    (3, [784, 128, 24], "bf16", 2e-2, 65, "fused"),            # fused kernel, 32-row logits tiles
+    (3, [784, 128, 24], "bf16", 2e-2, 4, "tiles"),
+    (3, [200, 96, 64, 10], "bf16", 2e-2, 4, "tiles"),          # three layers
+    (3, [512, 256, 128, 10], "bf16", 2e-2, 33, "streamed 2"),  # three layers, output kernel in two passes
 ])
-def test_training_with_a_scale_tensor_matches_oracle(i, dims, mode, rtol):
+def test_training_with_a_scale_tensor_matches_oracle(i, dims, mode, rtol, P, path):
     cfg = synthetic.config(i)
-    cfg["P"] = 4
+    cfg["P"] = P
     if dims:
         cfg["dims"] = dims
     data = synthetic.dataset(cfg, 600, 128)
@@ -131,13 +135,13 @@ def test_training_with_a_scale_tensor_matches_oracle(i, dims, mode, rtol):
             data[split] = ((yy + 10 * (np.arange(len(yy)) % 3)) % C).astype(yy.dtype)
     pop = _pop(cfg, data)
     B = cfg["batch"]
-    S = _paper_like(B, C, 17, 4)
+    S = _paper_like(B, C, 17, P)
     pop.set_grad_scale(S)
-    pop.train_epoch(0)
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
     s = pop.scores()
     n = len(data["y_train"])
     perm = oracle.permutation(cfg["seed"], 0, n)
-    for v in range(4):
+    for v in sorted({0, 1, 2, P - 1}):
         lr, _, th = oracle.variant_hparams(cfg["seed"], v, cfg["lr"], cfg.get("dens", (1.0, 1.0)), cfg.get("dens_list"))
         params, mask = oracle.variant_init(cfg["seed"], v, cfg["dims"], th)
         ce, _ = oracle.train_steps(mode, cfg["dims"], params, mask, lr, data["x_train"], data["y_train"], perm, B, 0,
@@ -148,18 +152,18 @@ def test_training_with_a_scale_tensor_matches_oracle(i, dims, mode, rtol):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("i", [1, 3])
-def test_scale_tensor_of_one_over_b_is_bitwise_the_scalar_path_on_gpu(i):
+@pytest.mark.parametrize("i,P,path", [(1, 4, "tiles"), (3, 33, "fused"), (3, 4, "tiles")])
+def test_scale_tensor_of_one_over_b_is_bitwise_the_scalar_path_on_gpu(i, P, path):
     cfg = synthetic.config(i)
-    cfg["P"] = 4
+    cfg["P"] = P
     B = cfg["batch"]
     data = synthetic.dataset(cfg, 4 * B, 128)                  # whole batches only
     runs = []
     for use in (False, True):
         pop = _pop(cfg, data)
         if use:
-            pop.set_grad_scale(np.full((4, B, cfg["dims"][-1]), np.float32(1.0 / B), np.float32))
-        pop.train_epoch(0)
-        runs.append([pop.export(v)["params"].tobytes() for v in range(4)])
+            pop.set_grad_scale(np.full((P, B, cfg["dims"][-1]), np.float32(1.0 / B), np.float32))
+        assert training_path(pop, lambda: pop.train_epoch(0)) == path
+        runs.append([pop.export(v)["params"].tobytes() for v in range(P)])
         pop.close()
-    assert [a == b for a, b in zip(*runs)] == [True] * 4
+    assert [a == b for a, b in zip(*runs)] == [True] * P
