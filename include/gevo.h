@@ -379,7 +379,7 @@ typedef enum {
   GEVO_KERNEL_OUT_TRAIN = 4,     /* output layer: loss, gradients, update */
   GEVO_KERNEL_OUT_PREDICT = 5,   /* output layer: loss and accuracy on the test split */
   GEVO_KERNEL_BWD = 6,           /* hidden backward GEMM */
-  GEVO_KERNEL_AUX = 7,           /* zeroing, reductions */
+  GEVO_KERNEL_AUX = 7,           /* zeroing, reductions, register images of masters */
   GEVO_KERNEL_FUSED_TRAIN = 8,   /* two-layer nets: whole SGD steps, one workgroup per variant */
   GEVO_KERNEL_WEIGHT_COPY = 9,   /* bf16 weight copies read by the prediction GEMM */
   GEVO_KERNEL_FWD_OUT = 10,      /* prediction: last hidden layer GEMM with the output layer fused */

@@ -145,20 +145,38 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
   //  - where the fused kernel does not take the net and the streaming kernel
   //    not every hidden layer (an epoch of 24 variants of 784-300-100-10, batch
   //    100: 5.3 ms with row-major operands, 2.8; 256 of 784-512-10, batch 128:
-  //    23.3 and 16.7; 250 of 1000-300-10, batch 200: 12.2 and 6.6);
+  //    23.3 and 16.7; 250 of 1000-300-10, batch 200: 12.2 and 6.6).  Not where it
+  //    takes a first layer with three quarters of the hidden weights (two thirds
+  //    at batch tile 256): that layer is bound by its master's traffic, which
+  //    tiles of 32 units, reading the rows four times as often, do not reach.
+  //    Streamed against tiles, ms a step, batch 256: 128 of 3072-1024-160-10 1.09
+  //    and 1.71, 64 of 3072-1024-700-10 0.87 and 1.15, 128 of 1024-512-320-10 0.43
+  //    and 0.51, 64 of 1024-512-480-10 (two thirds) 0.28 and 0.30; batch 128: 128 of 3072-1024-160-10 0.91 and 1.11, 64 of
+  //    1024-512-480-10 0.22 and 0.19.  A net whose second layer alone
+  //    would stream trains faster on tiles (batch 256: 64 of 200-320-768-10 0.29
+  //    and 0.22);
   //  - where those would leave most of the chip idle: they give a workgroup a
   //    variant or 128 units, these 32 units, so up to one workgroup per CU.
   //    Streamed: 16 variants of 3072-512-10, batch 128, 20 steps: 2.2 and 1.4
-  //    ms; 128 of them 8.3 and 10.4.  Fused, 47 steps of batch 128: 32
+  //    ms; 128 of them 8.3 and 10.4; where only the first layer streams, up to
+  //    two per CU (batch 256: 32 of 3072-512-96-10 0.22 and 0.21 ms a step, 48 of
+  //    them 0.25 and 0.34).  Fused, 47 steps of batch 128: 32
   //    variants of 784-256-10 2.09 and 1.42 ms, 64 of 784-128-10 1.64 and 1.40,
   //    100 of 784-256-10 2.10 and 3.29; its step is short for few inputs (16 of
   //    100-256-10: 0.66 and 0.85) and at smaller batches (48 of 784-128-10,
   //    batch 32: 1.3 and 2.0), so from 512 inputs and 97 rows up.
   int widest = 0;
-  for (int l = 0; l + 1 < y.L; ++l) widest = std::max(widest, y.lay[l].Np);
-  const bool few = (int64_t)y.P * (widest / 32) <= 256;
+  int64_t hidden = 0;
+  for (int l = 0; l + 1 < y.L; ++l) {
+    widest = std::max(widest, y.lay[l].Np);
+    hidden += (int64_t)y.lay[l].K * y.lay[l].N;
+  }
+  const int64_t first = (int64_t)y.lay[0].K * y.lay[0].N;
+  const bool streams = all_streamed ||
+                       (y.lay[0].streamed && (y.Bp == 256 ? 3 * first >= 2 * hidden : 4 * first >= 3 * hidden));
+  const bool few = (int64_t)y.P * (widest / 32) <= (all_streamed || y.fused ? 256 : 512);
   y.tiles = y.L > 1 && (c->dtype == GEVO_F32 ||
-                        (y.fused ? few && y.Bp == 128 && y.lay[0].Kp >= 512 && !y.resident : few || !all_streamed));
+                        (y.fused ? few && y.Bp == 128 && y.lay[0].Kp >= 512 && !y.resident : few || !streams));
   if (y.tiles) y.fused = false;
   for (int l = 0; l + 1 < y.L; ++l) {
     if (y.tiles) y.lay[l].streamed = false;
@@ -434,6 +452,10 @@ gevo_status forward_layer(gevo_pop* p, int l, const uint16_t* arows0, size_t ar0
   a.vtime = at<unsigned long long>(p, y.vtime);
   if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
   if (a.Kp % kTile || a.Np % kTile || a.R % kTile || a.R <= 0) return GEVO_E_SHAPE;
+  if (!q.streamed) {
+    HIP_TRY(launch_layer_train(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
+    return GEVO_OK;
+  }
   a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
   HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_FWD)));
   return GEVO_OK;
@@ -661,6 +683,10 @@ gevo_status train_step(gevo_pop* p, int t) {
       a.vtime = at<unsigned long long>(p, y.vtime);
       if (p->ragged) a.wout = at<uint32_t>(p, q.wout);
       if (a.Kp % kTile || a.Np % kTile || a.Bp % kTile || a.Bp > kPassRows) return GEVO_E_SHAPE;
+      if (!q.streamed) {
+        HIP_TRY(launch_layer_train(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
+        continue;
+      }
       a.Wimg = at<float>(p, q.wimg); a.mblk = at<uint32_t>(p, q.mblk);
       HIP_TRY(launch_stream_layer(a, y.P, p->stream, prof(p, GEVO_KERNEL_LAYER_TRAIN)));
     }

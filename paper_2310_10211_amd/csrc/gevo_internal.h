@@ -333,6 +333,8 @@ bool stream_layer_supported(int Kp, int Np, int Bp, int R);
 bool bwd_gemm_supported(int Kp, int Np, int Bp);
 hipError_t launch_bwd_gemm(const BwdArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev);
 hipError_t launch_stream_layer(const LayerArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev);
+// a training step of a hidden layer on the same operands for widths that it does not take (Bp 128 or 256)
+hipError_t launch_layer_train(const LayerArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev);
 size_t fused2_lds_bytes(int hp, int bp);     // 0 when the shape has no fused instantiation
 bool res2_supported(int Kp, int Hp, int Bp, int C);   // Kp 800, Hp 256, Bp 128, C <= 16
 int res2_max_pairs();                        // co-resident pairs on the current device (0: no cooperative launch)

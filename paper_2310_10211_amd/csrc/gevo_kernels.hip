@@ -240,6 +240,34 @@ __global__ __launch_bounds__(256) void k_init4(InitArgs a, int per) {
 }
 
 // ------------------------------------------------------------ hidden layer
+// The operand copy of a 32-unit tile's inputs [kb0, kb0 + kw) from the k-blocked
+// master into LDS, [32][WS], four 16-byte loads of a thread in flight.
+template <typename S>
+__device__ __forceinline__ void load_w_tile(S* wt, int WS, const float* Wv, int Np, int n0, int kb0, int kw) {
+  using O = Op<S>;
+  const int q = kw / 4;                                 // float4 per row
+  for (int i = threadIdx.x; i < 32 * q; i += 256 * 4) {
+    float4 w4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = i + u * 256;
+      // j in memory order: chunk j/256, row (j/8)%32, float4 j%8
+      w4[u] = j < 32 * q ? *reinterpret_cast<const float4*>(
+                               Wv + ((size_t)(kb0 / 32 + j / 256) * Np + n0 + (j / 8) % 32) * 32 + (j % 8) * 4)
+                         : make_float4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = i + u * 256;
+      if (j < 32 * q) {
+        S* dst = wt + ((j / 8) % 32) * WS + (j / 256) * 32 + (j % 8) * 4;
+        dst[0] = O::from_f32(w4[u].x); dst[1] = O::from_f32(w4[u].y);
+        dst[2] = O::from_f32(w4[u].z); dst[3] = O::from_f32(w4[u].w);
+      }
+    }
+  }
+}
+
 // Prediction rows of the shapes that the GEMM kernels do not take.  Workgroup
 // (n-tile of 32 output units, variant v); four waves.  The inputs k are
 // processed in blocks of KB columns (the block's operand copy of W fits in LDS):
@@ -273,28 +301,7 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
   // ---- fill the LDS operand tile with block blk
   auto fill = [&](int blk) {
     const int kb0 = blk * KB;
-    const int kw = min(KB, Kp - kb0);
-      const int q = kw / 4;                               // float4 per row
-      for (int i = threadIdx.x; i < 32 * q; i += 256 * 4) {
-        float4 w4[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int j = i + u * 256;
-          // j in memory order: chunk j/256, row (j/8)%32, float4 j%8
-          w4[u] = j < 32 * q ? *reinterpret_cast<const float4*>(
-                                   Wv + ((size_t)(kb0 / 32 + j / 256) * Np + n0 + (j / 8) % 32) * 32 + (j % 8) * 4)
-                             : make_float4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int j = i + u * 256;
-          if (j < 32 * q) {
-            S* dst = wt + ((j / 8) % 32) * WS + (j / 256) * 32 + (j % 8) * 4;
-            dst[0] = O::from_f32(w4[u].x); dst[1] = O::from_f32(w4[u].y);
-            dst[2] = O::from_f32(w4[u].z); dst[3] = O::from_f32(w4[u].w);
-          }
-        }
-      }
+    load_w_tile(wt, WS, Wv, Np, n0, kb0, min(KB, Kp - kb0));
     __syncthreads();
   };
 
@@ -341,6 +348,219 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
       if (nblk > 1) __syncthreads();
     }
     epilogue(row0, ntiles, acc);
+  }
+  vt_add(a.vtime, v, vt0);
+}
+
+// One training step of a bf16 hidden layer on row-major operands: the second
+// hidden layer of the nets whose first one streams (k_stream_layer writes and
+// k_bwd_gemm reads them) and whose second has no width for that kernel.
+// Workgroup (n-tile of 32 output units, variant v); four waves.  The inputs
+// k are processed in blocks of KB columns (the block's operand copy of W fits
+// in LDS).  Update (do_update), per 32-wide chunk c of a block, each wave
+// streaming its own chunks with the next chunk's weights already in flight:
+//   dW^T[n][k] = sum_b G[n][b] * A[k][b]          (MFMA, contraction = batch)
+// staged through LDS, then lane (row n, 16 columns) applies
+//   W[n][k]    = mask ? fl(W - fl(lr * dW)) : +0   (fp32 master, float4 in place)
+// and b[n] -= lr * sum_b G[n][b].  The updated block stays in LDS as an
+// operand, so the forward pass of the next step (do_forward) runs without
+// re-reading W, and the transposed copy for k_bwd_gemm is written from it:
+//   Z[r][n] = sum_k A_next[r][k] * W[n][k] + b[n],  A_out = relu(Z)  (MFMA)
+// Without do_update a block is loaded from the master (forward only).  Bound by
+// its operand loads, a cache line per lane; the layer is a small part of a net
+// that takes this path (the rule in make_layout).
+template <int BP>
+__global__ __launch_bounds__(256, 2) void k_layer_train(LayerArgs<uint16_t> a) {
+  typedef uint16_t S;
+  using O = Op<S>;
+  using F = typename O::Frag;
+  constexpr int KM = O::KM, KE = O::KE;
+  constexpr int NG = BP / KM;                        // contraction steps over the batch
+  constexpr int TPW = BP / 128;                      // row tiles per wave in the forward
+  constexpr int DSTR = 36;                           // fp32 staging row stride (16-byte aligned rows)
+  constexpr int SSTR = 32 + O::PAD;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ float bias_l[32];
+  const int KB = a.KB, WS = KB + O::PAD;
+  S* wt = reinterpret_cast<S*>(smem);                                // [32][WS] operand tile
+  float* stage = reinterpret_cast<float*>(smem + (size_t)32 * WS * sizeof(S));   // [4][32][DSTR]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int n0 = blockIdx.x * 32, v = blockIdx.y;
+  const uint64_t vt0 = vt_now();
+  if (a.wout && n0 >= (int)a.wout[v]) {                  // every unit of the tile removed
+    vt_add(a.vtime, v, vt0);
+    return;
+  }
+  const int Kp = a.Kp, Np = a.Np, kwords = Kp / 32;
+  float* Wv = a.Wm + (size_t)v * Np * Kp;                     // this variant, k-blocked
+  const uint32_t* mk = a.mask + ((size_t)v * Np + n0) * kwords;
+  const float lrv = a.lr[v];
+  float* dws = stage + wave * 32 * DSTR;
+  const int rn = lane >> 1, cs = (lane & 1) * 16;            // update ownership: row rn, columns cs..cs+15
+
+  F gf[NG];
+  if (a.do_update) {
+    const S* G = a.Gcols + v * a.g_vs;
+    // the gradient operand of dW first, so its loads are in flight with the
+    // bias gradient's (the bias store below would otherwise hold them back)
+    const S* gp = G + (size_t)(n0 + l32) * BP + lh * KE;
+#pragma unroll
+    for (int s2 = 0; s2 < NG; ++s2) gf[s2] = O::load(gp + s2 * KM);
+    // bias gradient of the 32 units: 8 lanes per unit, fixed-order reduction
+    const int nl = threadIdx.x >> 3, seg = threadIdx.x & 7, per = BP / 8;
+    const S* gr = G + (size_t)(n0 + nl) * BP + seg * per;
+    float s = 0.0f;
+    for (int b = 0; b < per; ++b) s += O::to_f32(gr[b]);
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    s += __shfl_xor(s, 4);
+    if (seg == 0) {
+      const float bo = a.bias[(size_t)v * Np + n0 + nl];
+      const bool bk = (a.bmask[(size_t)v * (Np / 32) + blockIdx.x] >> nl) & 1u;   // n0 = 32 blockIdx.x
+      const float bn = bk ? __fsub_rn(bo, __fmul_rn(lrv, s)) : 0.0f;
+      a.bias[(size_t)v * Np + n0 + nl] = bn;
+      bias_l[nl] = bn;
+    }
+  } else if (threadIdx.x < 32) {
+    bias_l[threadIdx.x] = a.bias[(size_t)v * Np + n0 + threadIdx.x];
+  }
+
+  // ---- fill the LDS operand tile with block blk (update or plain load), plus Wt
+  auto fill = [&](int blk) {
+    const int kb0 = blk * KB;
+    const int kw = min(KB, Kp - kb0);
+    const int nchb = kw / 32;
+    if (a.do_update) {
+      // row rn of the tile in 32-column chunk c of this block
+      auto wptr = [&](int c) { return Wv + ((size_t)(kb0 / 32 + c) * Np + n0 + rn) * 32 + cs; };
+      const uint32_t* mrow = mk + (size_t)rn * kwords + kb0 / 32;
+      const S* acb = a.Acols + v * a.ac_vs + (size_t)(kb0 + l32) * BP + lh * KE;
+      float4 nx[4];
+      uint32_t nmw = 0;
+      if (wave < nchb) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) nx[u] = *reinterpret_cast<const float4*>(wptr(wave) + 4 * u);
+        nmw = mrow[wave];
+      }
+      for (int c = wave; c < nchb; c += 4) {
+        float4 w4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w4[u] = nx[u];
+        const uint32_t mw = nmw;
+        if (c + 4 < nchb) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) nx[u] = *reinterpret_cast<const float4*>(wptr(c + 4) + 4 * u);
+          nmw = mrow[c + 4];
+        }
+        f32x16_t d0 = zero16(), d1 = zero16();
+        const S* ap = acb + (size_t)c * 32 * BP;
+#pragma unroll
+        for (int s2 = 0; s2 < NG; s2 += 2) {
+          d0 = O::mma(gf[s2], O::load(ap + s2 * KM), d0);
+          d1 = O::mma(gf[s2 + 1], O::load(ap + (s2 + 1) * KM), d1);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dws[crow(r, lane) * DSTR + l32] = d0[r] + d1[r];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        float dw[16];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float4 t = *reinterpret_cast<const float4*>(dws + rn * DSTR + cs + 4 * u);
+          dw[4 * u] = t.x; dw[4 * u + 1] = t.y; dw[4 * u + 2] = t.z; dw[4 * u + 3] = t.w;
+        }
+        float wn[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float w = (i & 3) == 0 ? w4[i >> 2].x : (i & 3) == 1 ? w4[i >> 2].y : (i & 3) == 2 ? w4[i >> 2].z : w4[i >> 2].w;
+          const bool keep = (mw >> (cs + i)) & 1u;
+          wn[i] = keep ? __fsub_rn(w, __fmul_rn(lrv, dw[i])) : 0.0f;
+        }
+        float* wdst = wptr(c);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          *reinterpret_cast<float4*>(wdst + 4 * u) = make_float4(wn[4 * u], wn[4 * u + 1], wn[4 * u + 2], wn[4 * u + 3]);
+        S* od = wt + rn * WS + c * 32 + cs;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) od[i] = O::from_f32(wn[i]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      }
+    } else {
+      load_w_tile(wt, WS, Wv, Np, n0, kb0, kw);
+    }
+    __syncthreads();
+    if (a.Wt) {
+      // transposed operand copy [k][n] for the backward of the layer above
+      for (int k = threadIdx.x >> 1; k < kw; k += 128) {
+        const int half = threadIdx.x & 1;
+        S* dst = a.Wt + (size_t)v * Kp * Np + (size_t)(kb0 + k) * Np + n0 + half * 16;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dst[i] = wt[(half * 16 + i) * WS + k];
+      }
+    }
+  };
+
+  // ---- forward over block blk, two accumulator chains per row tile
+  f32x16_t acc[TPW][2];
+#pragma unroll
+  for (int ti = 0; ti < TPW; ++ti) { acc[ti][0] = zero16(); acc[ti][1] = zero16(); }
+  auto forward = [&](int blk) {
+    const int kb0 = blk * KB;
+    const int kw = min(KB, Kp - kb0);
+#pragma unroll
+    for (int ti = 0; ti < TPW; ++ti) {
+      const S* ar = a.Arows + v * a.ar_vs + (size_t)((wave + 4 * ti) * 32 + l32) * Kp + kb0 + lh * KE;
+      const S* br = wt + l32 * WS + lh * KE;
+      int k = 0;
+      for (; k + 4 * KM <= kw; k += 4 * KM) {
+        F x[4], w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { x[u] = O::load(ar + k + u * KM); w[u] = O::load(br + k + u * KM); }
+        acc[ti][0] = O::mma(x[0], w[0], acc[ti][0]);
+        acc[ti][1] = O::mma(x[1], w[1], acc[ti][1]);
+        acc[ti][0] = O::mma(x[2], w[2], acc[ti][0]);
+        acc[ti][1] = O::mma(x[3], w[3], acc[ti][1]);
+      }
+      for (; k < kw; k += KM) acc[ti][0] = O::mma(O::load(ar + k), O::load(br + k), acc[ti][0]);
+    }
+  };
+
+  const int nblk = (Kp + KB - 1) / KB;
+  for (int blk = 0; blk < nblk; ++blk) {
+    fill(blk);
+    if (a.do_forward) forward(blk);
+    __syncthreads();
+  }
+  if (a.do_forward) {
+    // bias + ReLU, rows store, transposed store staged in LDS
+    S* sw = reinterpret_cast<S*>(dws);                        // [32][SSTR] per wave
+#pragma unroll
+    for (int ti = 0; ti < TPW; ++ti) {
+      const int row0 = (wave + 4 * ti) * 32;
+      const float bn = bias_l[l32];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl = crow(r, lane);
+        const float z = (acc[ti][0][r] + acc[ti][1][r]) + bn;
+        const S sv = O::from_f32(z > 0.0f ? z : 0.0f);
+        a.Orows[v * a.or_vs + (size_t)(row0 + rl) * Np + n0 + l32] = sv;
+        sw[l32 * SSTR + rl] = sv;                             // [n][row]
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      const int nl = lane >> 1, half = lane & 1;
+      S* dst = a.Ocols + v * a.oc_vs + (size_t)(n0 + nl) * BP + row0 + half * 16;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dst[i] = sw[nl * SSTR + half * 16 + i];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
   }
   vt_add(a.vtime, v, vt0);
 }
@@ -966,8 +1186,9 @@ hipError_t launch_init(const InitArgs& a, hipStream_t s, const LaunchEv& ev) {
   return hipGetLastError();
 }
 
-int layer_block_cols(int Kp, int elt, int pad) {
-  int cap = (int)(kLayerLds / (32 * (size_t)elt)) - pad;
+// columns per LDS block of an operand tile beside which `stage` bytes are kept
+int layer_block_cols(int Kp, int elt, int pad, size_t stage) {
+  int cap = (int)((kLayerLds - stage) / (32 * (size_t)elt)) - pad;
   cap = cap / 32 * 32;
   const int nblk = (Kp + cap - 1) / cap;
   return round_up((Kp + nblk - 1) / nblk, 32);
@@ -976,7 +1197,7 @@ int layer_block_cols(int Kp, int elt, int pad) {
 template <typename S>
 hipError_t launch_layer(const LayerArgs<S>& a0, int P, hipStream_t s, const LaunchEv& ev) {
   LayerArgs<S> a = a0;
-  a.KB = layer_block_cols(a.Kp, (int)sizeof(S), Op<S>::PAD);
+  a.KB = layer_block_cols(a.Kp, (int)sizeof(S), Op<S>::PAD, 0);
   const size_t lds = (size_t)32 * (a.KB + Op<S>::PAD) * sizeof(S);
   const dim3 grid(a.Np / 32, P);
   static bool attr = false;
@@ -987,6 +1208,30 @@ hipError_t launch_layer(const LayerArgs<S>& a0, int P, hipStream_t s, const Laun
   }
   hipExtLaunchKernelGGL((k_layer<S>), grid, dim3(256), lds, s, ev.start, ev.stop, 0, a);
   return hipGetLastError();
+}
+
+template <int BP>
+static hipError_t launch_lt(LayerArgs<uint16_t> a, int P, hipStream_t s, const LaunchEv& ev) {
+  constexpr size_t stage = (size_t)4 * 32 * 36 * 4;
+  a.KB = layer_block_cols(a.Kp, 2, Op<uint16_t>::PAD, stage);
+  static bool attr = false;
+  if (!attr) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer_train<BP>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLayerLds);
+    attr = true;
+  }
+  hipExtLaunchKernelGGL((k_layer_train<BP>), dim3(a.Np / 32, P), dim3(256),
+                        (size_t)32 * (a.KB + Op<uint16_t>::PAD) * 2 + stage, s, ev.start, ev.stop, 0, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_layer_train(const LayerArgs<uint16_t>& a, int P, hipStream_t s, const LaunchEv& ev) {
+  if (a.Kp % 32 || a.Np % 32 || a.Kp <= 0 || a.Np <= 0 || !(a.do_update || a.do_forward) ||
+      (a.do_forward && a.R != a.Bp))
+    return hipErrorInvalidValue;
+  if (a.Bp == 128) return launch_lt<128>(a, P, s, ev);
+  if (a.Bp == 256) return launch_lt<256>(a, P, s, ev);
+  return hipErrorInvalidValue;
 }
 
 template <typename S>

@@ -227,6 +227,7 @@ def test_bf16_two_layer_shapes(dims, batch, n_train, P, path):
     (3, None, None, 3, "tiles"),
     (5, [1024, 256, 128, 10], 256, 33, "streamed 2"),    # hidden layers on the streaming kernel's register-image masters
     (5, [1024, 256, 128, 10], 256, 3, "tiles"),
+    (5, [1024, 256, 96, 10], 256, 65, "streamed 1"),     # one layer on a register image, one on the k-blocked master
 ])
 def test_export_import_round_trip_between_epochs_is_exact(i, dims, batch, P, path):
     """Exporting and re-importing every variant between epochs (the register-image
@@ -300,6 +301,7 @@ def test_bf16_three_layer():
     ([512, 128, 256, 10], 100, 730, 33, "streamed 2"),     # batch tile 128
     ([512, 128, 256, 10], 100, 730, 3, "tiles"),
     ([3072, 192, 128, 10], 256, 800, 65, "tiles"),         # the first hidden layer (192 units) has no streaming width
+    ([3072, 256, 160, 10], 256, 700, 65, "streamed 1"),    # first layer streamed, 160 units of the second beside it
     ([3072, 256, 160, 10], 256, 700, 3, "tiles"),
     ([1024, 384, 256, 10], 128, 700, 22, "streamed 2"),    # three 128-unit tiles per variant, batch tile 128
     ([1024, 384, 256, 10], 128, 700, 3, "tiles"),
@@ -307,7 +309,8 @@ def test_bf16_three_layer():
 def test_bf16_deep_nets_on_the_streaming_layer_kernel(dims, batch, n_train, P, path):
     """Hidden layers whose widths are multiples of 128 and whose inputs are
     multiples of 64, at batch tiles 128 and 256, train through the streaming
-    hidden-layer kernel; other nets and small populations on the tile kernels."""
+    hidden-layer kernel, a second layer of another width beside a streamed
+    first one; other nets and small populations on the tile kernels."""
     cfg, data = _small(5, P=P, n_train=n_train, n_test=400, dims=dims, batch=batch)
     if dims[0] != 3072:
         data["x_train"] = data["x_train"][:, :dims[0]].copy()

@@ -117,6 +117,11 @@ def _one_step_case(cfg, data, variants, path, seed=5):
     ([512, 128, 10], 250, 300, 65, "streamed 1"),           # one hidden layer, no backward GEMM
     ([3072, 1024, 512, 10], 256, 512, 9, "streamed 2"),     # the full width of the 128-variant CIFAR-shaped workload
     ([3072, 1024, 512, 10], 256, 512, 2, "tiles"),
+    ([1024, 256, 160, 10], 256, 300, 65, "streamed 1"),     # the first layer streamed, the second beside it
+    ([1024, 256, 160, 10], 256, 300, 64, "tiles"),
+    ([512, 384, 70, 10], 128, 300, 43, "streamed 1"),       # a ragged second layer, batch tile 128
+    ([512, 1024, 96, 10], 120, 300, 17, "streamed 1"),      # its inputs in two LDS blocks
+    ([512, 256, 192, 10], 128, 300, 65, "tiles"),           # less than three quarters of the weights in the first
 ])
 def test_streamed_net_one_step_elementwise(dims, batch, n_train, P, path):
     cfg = synthetic.config(5, P=P, dims=dims, batch=batch, lr=(0.05, 0.05))

@@ -188,6 +188,7 @@ def _struct_reference(cfg, genome, lr_base):
     (3, [200, 128, 64, 10], 128, "tiles"),                     # and in bf16
     (5, [1024, 256, 128, 10], 33, "streamed 2"),               # a removed 128-unit tile of the streaming kernel
     (5, [1024, 256, 128, 10], 4, "tiles"),
+    (5, [1024, 256, 96, 10], 65, "streamed 1"),                # removed tiles of the layer beside a streamed one
 ])
 def test_structural_genomes_rebuild_and_train_like_the_oracle(i, dims, P, path):
     cfg, data = _small(i, P=P, n_train=640, n_test=256)
