@@ -90,6 +90,13 @@ typedef enum { GEVO_INIT_XAVIER = 0, GEVO_INIT_BASE_NOISE = 1 } gevo_init;
  * weight of the base model by (1 + noise_rel_std * eps); the base model is
  * base_params (host array, canonical layout: per layer W_l in x out then b_l)
  * or, if NULL, the seeded Xavier model.  n_train may be 0 (prediction only).
+ *
+ * The same configuration gives the same bits on every run.  A variant's sums
+ * are ordered by its index v and, in training, by P: which kernel trains a
+ * layer and how the kernel divides it follow the population's size.  So a
+ * variant trained in a population of another size holds the same masks,
+ * initial weights and data order, and weights and losses that agree to the
+ * rounding of the operand type.
  */
 typedef struct {
   uint32_t abi_version;               /* must be GEVO_ABI_VERSION */

@@ -392,6 +392,7 @@ def test_masked_weights_stay_plus_zero_and_divergence_is_contained(P, path):
 
 
 def test_variants_are_independent_of_population_size():
+    """Two sizes that train in the same kernel (test_gpu_population_size.py has the others)."""
     cfg8, data = _small(3, P=8, n_train=640, n_test=256)
     cfg3 = dict(cfg8, P=3)
     a = _pop(cfg8, data)
