@@ -57,3 +57,52 @@ def test_three_steps_and_prediction_match_the_oracle(dims, batch, P):
         assert abs(s["test_loss"][v] - ref[v]["test_loss"]) <= 1e-5 * abs(ref[v]["test_loss"])
         assert abs(s["test_acc"][v] - ref[v]["test_acc"]) <= 1.0 / n_test      # a tie within rounding
     pop.close()
+
+
+# (unit tiles, row tiles) per wave of the prediction kernel: rounds of 256
+# workgroups times the products of a wave, one more for the operands
+TILES = [(2, 8), (2, 4), (1, 4), (1, 2), (1, 1)]
+
+
+def _tile(width, rows, P):
+    nb, nrt = -(-width // 32), rows // 32
+
+    def cost(t):
+        nt, rt = t
+        return -(-(-(-nb // (4 * nt)) * -(-nrt // rt) * P) // 256) * (nt * rt + 1)
+    return min(TILES, key=cost)
+
+
+@pytest.mark.parametrize("dims,P,n_test,tiles", [
+    ([784, 256, 10], 64, 2300, [(2, 8), (1, 4)]),           # two chunks of rows, the second ragged
+    ([100, 224, 10], 64, 4500, [(2, 8), (2, 8), (2, 4)]),   # seven unit tiles on waves of two
+    ([100, 256, 10], 128, 250, [(2, 4)]),
+    ([100, 160, 7], 100, 400, [(2, 8)]),                    # five
+    ([100, 96, 10], 40, 200, [(1, 2)]),
+    ([100, 40, 3], 5, 2049, [(1, 2), (1, 1)]),
+    ([200, 96, 224, 10], 64, 2048, [(1, 4), (2, 8)]),       # two hidden layers
+])
+def test_prediction_tiles_match_the_oracle(dims, P, n_test, tiles):
+    """fp32 prediction on every tile of the forward kernel, over one to three
+    chunks of 2,048 rows."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2310_10211_amd as g
+    pad = -(-n_test // 256) * 256
+    chunks = [min(2048, pad - c) for c in range(0, pad, 2048)]
+    assert [_tile(w, r, P) for r in chunks for w in dims[1:-1]] == tiles
+    cfg = synthetic.config(2, P=P, dims=dims, dens=(0.5, 1.0))
+    data = synthetic.dataset(cfg, 0, n_test)
+    x, y = np.ascontiguousarray(data["x_test"][:, :dims[0]]), data["y_test"] % dims[-1]
+    data = dict(x_train=data["x_train"], y_train=data["y_train"], x_test=x, y_test=y)
+    print(f"[gpu] prediction tiles dims={dims} P={P} n_test={n_test}", flush=True)
+    pop = g.Population(cfg, None, None, x, y)
+    pop.predict()
+    s = pop.scores()
+    pop.close()
+    sample = sorted({0, 1, P - 1})
+    ref = oracle.evaluate(cfg, data, variants=sample, epochs=0, mode="f32")
+    for v in sample:                                         # fp32 sums of at most 800 terms, means of n_test losses
+        assert abs(s["test_loss"][v] - ref[v]["test_loss"]) <= 1e-5 * abs(ref[v]["test_loss"]), v
+        assert abs(s["test_acc"][v] - ref[v]["test_acc"]) <= 1.0 / n_test, v
