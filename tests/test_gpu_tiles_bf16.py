@@ -17,9 +17,10 @@ CASES = [
     ([40, 33, 3], 150, 3), ([100, 64, 32], 180, 3), ([40, 96, 3], 220, 3), ([300, 64, 10], 256, 3),
     ([20, 30, 2], 7, 2),                                             # one input block: three waves have none
     ([70, 64, 5], 20, 256), ([200, 64, 10], 128, 256),               # two unit tiles per workgroup
+    ([60, 160, 7], 60, 64), ([60, 192, 7], 200, 86),                 # five; three pairs, two of them removed
     ([200, 70, 40, 10], 50, 4), ([130, 64, 160, 6], 100, 60),        # three layers
     ([520, 256, 10], 128, 4), ([600, 100, 10], 100, 5),              # few variants of nets the fused kernel takes
-    ([512, 128, 10], 200, 3), ([512, 128, 128, 5], 128, 3),          # and of nets the streaming kernel takes
+    ([512, 128, 10], 200, 3), ([512, 128, 10], 250, 3), ([512, 128, 128, 5], 128, 3),   # and the streaming kernel (not 200 rows)
 ]
 
 
@@ -59,11 +60,26 @@ def test_bf16_tiles_match_the_oracle(dims, batch, P):
         assert np.array_equal(e["mask"], init[v]["mask"])
         assert abs(s["train_loss"][v] - ref[v]["train_loss"][0]) <= 2e-2 * abs(ref[v]["train_loss"][0])
         assert abs(s["test_loss"][v] - ref[v]["test_loss"]) <= 2e-2 * abs(ref[v]["test_loss"])
-    # a narrowed variant trains like the oracle's, its neighbours undisturbed
+    # a narrowed variant trains like the oracle's, its neighbours like those of
+    # a population without it (the workgroups of its removed unit tiles return)
     if len(dims) == 3 and dims[1] > 40:
-        pop.set_genomes([[(g.EDIT_WIDTH, 1, 20)] if v == 1 else [] for v in range(P)], 0.05)
-        pop.train_epoch(0)
-        e = pop.export(1)
-        W1 = e["params"][:dims[0] * dims[1]].reshape(dims[0], dims[1])
-        assert np.all(W1[:, 20:] == 0) and np.any(W1[:, :20] != 0) and np.all(np.isfinite(pop.scores()["train_loss"]))
+        runs = []
+        for narrow in (True, False):
+            pop.set_genomes([[(g.EDIT_WIDTH, 1, 20)] if v == 1 and narrow else [] for v in range(P)], 0.05)
+            pop.train_epoch(0)
+            runs.append([pop.export(v)["params"] for v in (0, 1, P - 1)])
+            assert np.all(np.isfinite(pop.scores()["train_loss"]))
+        for i in (0, 2):
+            if (0, 1, P - 1)[i] != 1:
+                assert runs[0][i].tobytes() == runs[1][i].tobytes(), i
+        mask, bmask = oracle.structure_masks(dims, [dims[0], 20, dims[2]], [1, 1], oracle.genome_mask(cfg["seed"], dims, [], []))
+        start, _ = oracle.variant_init(cfg["seed"], 0, dims, 1 << 24)
+        n1 = dims[0] * dims[1]
+        start[:n1] *= mask[:n1]
+        start[n1 + dims[1]:n1 + dims[1] + dims[1] * dims[2]] *= mask[n1:]
+        p = start.copy()
+        oracle.train_steps("bf16", dims, p, mask, 0.05, data["x_train"], data["y_train"], perm, batch, 0, 3, bmask=bmask)
+        got = runs[0][1].astype(np.float64)
+        assert np.all(got[p == 0] == 0)
+        assert np.linalg.norm(got - p) <= 2.0 ** -7 * np.linalg.norm(p - start)
     pop.close()
