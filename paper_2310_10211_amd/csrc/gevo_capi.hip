@@ -128,6 +128,8 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
     q.Kp = round_up(q.K, kTile);
     q.Np = (l == y.L) ? kTile : round_up(q.N, kTile);
   }
+  // (asked of every net, so that what is accepted depends on its shape alone,
+  // not on the kernels that train it: those on tile images hold no such operand)
   if (out_lds(y.lay[y.L - 1].Kp, y.Bp, y.elt, pad) > kLdsBudget) return GEVO_E_UNSUPPORTED;
   y.fused = y.L == 2 && c->dtype == GEVO_BF16 && fused2_lds_bytes(y.lay[0].Np, y.Bp) > 0;
   y.resident = y.fused && res2_supported(y.lay[0].Kp, y.lay[0].Np, y.Bp, (int)c->dims[2]) && resident_requested();
@@ -151,10 +153,10 @@ gevo_status make_layout(const gevo_pop_config* c, Layout* o) {
   //    tiles of 32 units, reading the rows four times as often, do not reach.
   //    Streamed against tiles, ms a step, batch 256: 128 of 3072-1024-160-10 1.09
   //    and 1.71, 64 of 3072-1024-700-10 0.87 and 1.15, 128 of 1024-512-320-10 0.43
-  //    and 0.51, 64 of 1024-512-480-10 (two thirds) 0.28 and 0.30; batch 128: 128 of 3072-1024-160-10 0.91 and 1.11, 64 of
-  //    1024-512-480-10 0.22 and 0.19.  A net whose second layer alone
-  //    would stream trains faster on tiles (batch 256: 64 of 200-320-768-10 0.29
-  //    and 0.22);
+  //    and 0.51, 64 of 1024-512-480-10 (two thirds) 0.28 and 0.30; batch 128: 128
+  //    of 3072-1024-160-10 0.91 and 1.11, 64 of 1024-512-480-10 0.22 and 0.19.  A
+  //    net whose second layer alone would stream trains faster on tiles (batch
+  //    256: 64 of 200-320-768-10 0.29 and 0.22);
   //  - where those would leave most of the chip idle: they give a workgroup a
   //    variant or 128 units, these 32 units, so up to one workgroup per CU.
   //    Streamed: 16 variants of 3072-512-10, batch 128, 20 steps: 2.2 and 1.4
@@ -841,44 +843,40 @@ struct PredictBufs {
 
 LaunchEv pev(gevo_pop* p, const PredictBufs& b, int kind) { return b.profile ? prof(p, kind) : LaunchEv{}; }
 
-// forward of hidden layer l of variants [v0, v0 + G) over R prediction rows
-template <typename S>
-gevo_status predict_layer(gevo_pop* p, const PredictBufs& b, int l, const S* arows, size_t ar_vs, int R) {
+// forward of bf16 hidden layer l of variants [v0, v0 + G) over R prediction rows
+gevo_status predict_layer(gevo_pop* p, const PredictBufs& b, int l, const uint16_t* arows, size_t ar_vs, int R) {
   const Layout& y = p->y;
   const LayerLay& q = y.lay[l];
-  const size_t v0 = (size_t)b.v0;
-  LayerArgs<S> a{};
-  a.Kp = q.Kp; a.Np = q.Np; a.Bp = y.Bp;
-  a.Wm = at<float>(p, q.Wm) + v0 * q.Np * q.Kp; a.bias = at<float>(p, q.bias) + v0 * q.Np;
-  a.mask = at<uint32_t>(p, q.mask) + v0 * q.Np * (q.Kp / 32); a.bmask = at<uint32_t>(p, q.bmask) + v0 * (q.Np / 32);
-  a.lr = at<float>(p, y.lr) + v0;
-  a.do_update = 0;
-  a.do_forward = 1;
+  const size_t v0 = (size_t)b.v0, o_vs = (size_t)kPredictChunk * q.Np;
+  float* Wm = at<float>(p, q.Wm) + v0 * q.Np * q.Kp;
+  float* bias = at<float>(p, q.bias) + v0 * q.Np;
+  uint16_t* O = static_cast<uint16_t*>(b.act[l]);
+  unsigned long long* vtime = at<unsigned long long>(p, y.vtime) + v0;
+  if (q.Kp % kTile || q.Np % kTile || R % kTile || R <= 0) return GEVO_E_SHAPE;
+  if (b.wbf[l] && pred_gemm_supported(q.Kp, q.Np, R)) {
+    PredGemmArgs g{};
+    g.A = arows; g.a_vs = ar_vs; g.W = b.wbf[l]; g.bias = bias; g.O = O; g.o_vs = o_vs;
+    g.Kp = q.Kp; g.Np = q.Np; g.R = R; g.P = b.G;
+    g.vtime = vtime;
+    HIP_TRY(launch_pred_gemm(g, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+    return GEVO_OK;
+  }
+  if (fwd_gemm_supported(q.Kp, q.Np, R)) {                     // plain per-variant GEMM, fp32 weights
+    FwdGemmArgs g{};
+    g.A = arows; g.a_vs = ar_vs; g.Wm = Wm; g.bias = bias; g.O = O; g.o_vs = o_vs;
+    g.Kp = q.Kp; g.Np = q.Np; g.R = R; g.P = b.G;
+    g.vtime = vtime;
+    HIP_TRY(launch_fwd_gemm(g, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+    return GEVO_OK;
+  }
+  LayerArgs<uint16_t> a{};
+  a.Kp = q.Kp; a.Np = q.Np;
+  a.Wm = Wm; a.bias = bias;
   a.R = R;
   a.Arows = arows; a.ar_vs = ar_vs;
-  a.Orows = static_cast<S*>(b.act[l]); a.or_vs = (size_t)kPredictChunk * q.Np;
-  a.vtime = at<unsigned long long>(p, y.vtime) + v0;
-  if (a.Kp % kTile || a.Np % kTile || a.R % kTile || a.R <= 0) return GEVO_E_SHAPE;
-  if constexpr (std::is_same<S, uint16_t>::value) {
-    if (b.wbf[l] && pred_gemm_supported(q.Kp, q.Np, R)) {
-      PredGemmArgs g{};
-      g.A = arows; g.a_vs = ar_vs; g.W = b.wbf[l]; g.bias = a.bias; g.O = a.Orows; g.o_vs = a.or_vs;
-      g.Kp = q.Kp; g.Np = q.Np; g.R = R; g.P = b.G;
-      g.vtime = a.vtime;
-      HIP_TRY(launch_pred_gemm(g, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
-      return GEVO_OK;
-    }
-    if (fwd_gemm_supported(a.Kp, a.Np, a.R)) {                 // plain per-variant GEMM, fp32 weights
-      FwdGemmArgs g{};
-      g.A = arows; g.a_vs = ar_vs; g.Wm = a.Wm; g.bias = a.bias; g.O = a.Orows; g.o_vs = a.or_vs;
-      g.Kp = a.Kp; g.Np = a.Np; g.R = a.R; g.P = b.G;
-      g.vtime = a.vtime;
-      HIP_TRY(launch_fwd_gemm(g, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
-      return GEVO_OK;
-    }
-  }
-  if constexpr (std::is_same<S, uint16_t>::value)             // full-precision hidden layers: launch_tile_fwd
-    HIP_TRY(launch_layer<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+  a.Orows = O; a.or_vs = o_vs;
+  a.vtime = vtime;
+  HIP_TRY(launch_layer<uint16_t>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
   return GEVO_OK;
 }
 
@@ -909,17 +907,15 @@ gevo_status predict_pass(gevo_pop* p, const PredictBufs& b) {
       const LayerLay& q = y.lay[l];
       const S* ain = l == 0 ? xr : static_cast<const S*>(b.act[l - 1]);
       const size_t a_vs = l == 0 ? 0 : (size_t)kPredictChunk * y.lay[l - 1].Np;
-      if constexpr (std::is_same<S, float>::value) {
-        if (y.tiles) {
-          TileFwdArgs<S> a{};
-          a.Kp = q.Kp; a.Np = q.Np; a.R = R;
-          a.Wm = at<float>(p, q.Wm) + v0 * q.Np * q.Kp; a.bias = at<float>(p, q.bias) + v0 * q.Np;
-          a.Xrows = ain; a.xr_vs = a_vs;
-          a.Orows = static_cast<S*>(b.act[l]); a.or_vs = (size_t)kPredictChunk * q.Np;
-          a.vtime = at<unsigned long long>(p, y.vtime) + v0;
-          HIP_TRY(launch_tile_fwd<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
-          continue;
-        }
+      if constexpr (std::is_same<S, float>::value) {             // full-precision hidden layers are tile images
+        TileFwdArgs<S> a{};
+        a.Kp = q.Kp; a.Np = q.Np; a.R = R;
+        a.Wm = at<float>(p, q.Wm) + v0 * q.Np * q.Kp; a.bias = at<float>(p, q.bias) + v0 * q.Np;
+        a.Xrows = ain; a.xr_vs = a_vs;
+        a.Orows = static_cast<S*>(b.act[l]); a.or_vs = (size_t)kPredictChunk * q.Np;
+        a.vtime = at<unsigned long long>(p, y.vtime) + v0;
+        HIP_TRY(launch_tile_fwd<S>(a, b.G, p->stream, pev(p, b, GEVO_KERNEL_LAYER_FWD)));
+        continue;
       }
       if constexpr (std::is_same<S, uint16_t>::value) {
         if (b.wbf[l] && l == y.L - 2 && q.Np == 256 && o.Kp == 256 && pred_gemm_supported(q.Kp, q.Np, R)) {
@@ -935,9 +931,9 @@ gevo_status predict_pass(gevo_pop* p, const PredictBufs& b) {
           fused = true;
           continue;
         }
+        gevo_status st = predict_layer(p, b, l, ain, a_vs, R);
+        if (st != GEVO_OK) return st;
       }
-      gevo_status st = predict_layer<S>(p, b, l, ain, a_vs, R);
-      if (st != GEVO_OK) return st;
     }
     if (fused) continue;
     if constexpr (std::is_same<S, float>::value) {

@@ -928,7 +928,7 @@ gevo_status cnn_predict_segments(gevo_cnn* h) {
         const int j = g.s0 - 1;
         a.src = at<const uint16_t>(ws, (k - 1) & 1 ? y.actB : y.actA); a.src_vs = y.mid_vs[(k - 1) & 1];
         a.src_px = y.hin[j + 1] * y.win[j + 1]; a.src_c = chan(j);
-        a.src_off = 0; a.src_ps = seg_ps(a.src_c); a.src_img = a.src_px * a.src_ps;
+        a.src_off = 0; a.src_ps = seg_ps(a.src_c);
         a.c8_magic = cnn_magic(a.src_c / 8);
       }
       const bool tail = k + 1 == y.nseg;

@@ -50,7 +50,7 @@ struct CnnSegArgs {
   int im, im2;                                    // LDS byte offsets of the padded bf16 images and their copy
                                                   // one element further on
   const uint16_t* src; size_t src_vs;             // source map, elements per variant
-  int src_px, src_c, src_off, src_ps, src_img;    // pixels, channels; LDS offset, bytes per pixel and image
+  int src_px, src_c, src_off, src_ps;             // pixels, channels; LDS offset, bytes per pixel
   uint32_t c8_magic;                              // ceil(2^32 / (src_c / 8))
   int nst;
   CnnSegStage st[kSegMaxStages];

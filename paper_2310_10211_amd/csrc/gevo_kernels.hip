@@ -286,10 +286,6 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
   const int l32 = lane & 31, lh = lane >> 5;
   const int n0 = blockIdx.x * 32, v = blockIdx.y;
   const uint64_t vt0 = vt_now();
-  if (a.wout && n0 >= (int)a.wout[v]) {                  // every unit of the tile removed
-    vt_add(a.vtime, v, vt0);
-    return;
-  }
   const int Kp = a.Kp, Np = a.Np;
   const float* Wv = a.Wm + (size_t)v * Np * Kp;               // this variant, k-blocked
   if (threadIdx.x < 32) bias_l[threadIdx.x] = a.bias[(size_t)v * Np + n0 + threadIdx.x];
@@ -869,7 +865,8 @@ __global__ __launch_bounds__(256) void k_out_fwd(OutArgs<S> a) {
 // the masked SGD update to those columns of the master; waves 1-3 form
 // G_{L-1}[k][b] = (sum_c W_L[c][k] G[b][c]) * [A[k][b] > 0] for the same
 // inputs from the columns' pre-update values, one 32-row batch tile at a
-// time.  The kt == 0 workgroup also
+// time (bf16 only: full-precision nets that come here have no hidden layer).
+// The kt == 0 workgroup also
 // updates the biases and adds the CE and hit sums, tiles in order.  Each
 // workgroup alone reads and writes its columns, so no other workgroup sees
 // a half-updated W_L.
@@ -930,31 +927,27 @@ __global__ __launch_bounds__(256) void k_out_upd(OutArgs<S> a) {
       const int i = threadIdx.x + u * 256;
       gv[u] = i < nvec ? gsrc[i] : make_uint4(0, 0, 0, 0);
     }
-    const float4 wv = reinterpret_cast<const float4*>(a.Wm + ((size_t)v * (Kp / 32) + kt) * 32 * 32)[threadIdx.x];
+    float4 wv{};
+    if constexpr (sizeof(S) == 2)
+      wv = reinterpret_cast<const float4*>(a.Wm + ((size_t)v * (Kp / 32) + kt) * 32 * 32)[threadIdx.x];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int i = threadIdx.x + u * 256;
       if (i < nvec) {
         const S* e = reinterpret_cast<const S*>(&gv[u]);
         const int row = (i * PER) >> 5, col = (i * PER) & 31;
-        if constexpr (sizeof(S) == 2) {
+        if constexpr (sizeof(S) == 2)
           *reinterpret_cast<uint4*>(gs + row * GSTR + col) = gv[u];   // GSTR * 2 = 80 bytes: 16-byte aligned
-        } else {
-#pragma unroll
-          for (int j = 0; j < PER; ++j) gs[row * GSTR + col + j] = e[j];
-        }
 #pragma unroll
         for (int j = 0; j < PER; ++j) gT[(col + j) * BT + row] = e[j];
       }
     }
-    // k-blocked master tile [c][32 k]: thread t holds class t / 8, inputs 4 (t % 8) .. +3
-    S* wd = wold + (threadIdx.x >> 3) * WSTR + (threadIdx.x & 7) * 4;
     if constexpr (sizeof(S) == 2) {                     // WSTR * 2 = 80 bytes: 8-byte aligned pieces
+      // k-blocked master tile [c][32 k]: thread t holds class t / 8, inputs 4 (t % 8) .. +3
+      S* wd = wold + (threadIdx.x >> 3) * WSTR + (threadIdx.x & 7) * 4;
       const uint32_t lo = (uint32_t)O::from_f32(wv.x) | (uint32_t)O::from_f32(wv.y) << 16;
       const uint32_t hi = (uint32_t)O::from_f32(wv.z) | (uint32_t)O::from_f32(wv.w) << 16;
       *reinterpret_cast<uint2*>(wd) = make_uint2(lo, hi);
-    } else {
-      wd[0] = O::from_f32(wv.x); wd[1] = O::from_f32(wv.y); wd[2] = O::from_f32(wv.z); wd[3] = O::from_f32(wv.w);
     }
   }
   __syncthreads();
@@ -1006,7 +999,7 @@ __global__ __launch_bounds__(256) void k_out_upd(OutArgs<S> a) {
       *reinterpret_cast<float4*>(Wmv + ((size_t)kt * 32 + rn) * 32 + cs + 4 * u) =
           make_float4(wn[4 * u], wn[4 * u + 1], wn[4 * u + 2], wn[4 * u + 3]);
   }
-  if (a.Gcols) {
+  if constexpr (sizeof(S) == 2) if (a.Gcols) {
     // gradient of the last hidden layer for inputs kt*32 .. +31, batch-contiguous, with ReLU'
     for (int bt = wave - 1; wave > 0 && bt < ntile; bt += 3) {   // waves 1-3 (wave 0 has dW)
       float av[16];
@@ -1032,13 +1025,9 @@ __global__ __launch_bounds__(256) void k_out_upd(OutArgs<S> a) {
         S* gr = a.Grows + v * a.gr_vs + (size_t)b * Kp + kt * 32 + 4 * lh;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if constexpr (sizeof(S) == 2) {
-            const uint32_t lo = (uint32_t)g[4 * q] | (uint32_t)g[4 * q + 1] << 16;
-            const uint32_t hi = (uint32_t)g[4 * q + 2] | (uint32_t)g[4 * q + 3] << 16;
-            *reinterpret_cast<uint2*>(gr + 8 * q) = make_uint2(lo, hi);
-          } else {
-            *reinterpret_cast<float4*>(gr + 8 * q) = make_float4(g[4 * q], g[4 * q + 1], g[4 * q + 2], g[4 * q + 3]);
-          }
+          const uint32_t lo = (uint32_t)g[4 * q] | (uint32_t)g[4 * q + 1] << 16;
+          const uint32_t hi = (uint32_t)g[4 * q + 2] | (uint32_t)g[4 * q + 3] << 16;
+          *reinterpret_cast<uint2*>(gr + 8 * q) = make_uint2(lo, hi);
         }
       }
     }
