@@ -621,7 +621,12 @@ int seg_image(int H, int W, int C) { return 2 * ((2 * seg_pitch(H, W, C) + 64 + 
 // Map j (the output of depthwise layer j) is hin[j + 1] x win[j + 1] x (stem or
 // ch[j - 1]).  A segment alternates between two LDS regions: its source map
 // (or, with the stem, map 0) and every second map after it in x, the others
-// (and the padded images before the stem) in y.
+// (and the padded images before the stem) in y.  Whole segments measured faster
+// than the layers on every net tried, so they run whenever the maps fit (ms per
+// prediction, layers and segments: 64 variants of the 32x32 net, stem 32, blocks
+// 128 to 512, 10,000 images 138.8 and 66.6; 16 of a 24x24 net, 2,000 images 14.2
+// and 4.6; 32 of a 32x32x4 net with 256 channels at full size, 1,000 images 19.9
+// and 7.4; 64 of 4x4x3, 4,000 images 4.0 and 1.3).
 void cnn_plan_segments(CnnLayout& y) {
   y.nseg = 0;
   auto chan = [&](int j) { return j == 0 ? y.stem : y.ch[j - 1]; };
@@ -657,7 +662,11 @@ void cnn_plan_segments(CnnLayout& y) {
     // Whole rest of the net if four images of it fit.  Otherwise up to the
     // first map small enough that a later segment holds several images of
     // it: the deep layers have most of the weights, which a segment reads once
-    // per group.  Otherwise as far as one image fits.
+    // per group.  Otherwise as far as one image fits.  (The 32x32 net, 66.6 ms so:
+    // the rest from one image up 80.5, from two the same plan.  16x16x1 with blocks
+    // 2x128, 1x256, 2x512, 64 variants, 4,000 images: four 7.1 ms, eight images
+    // 9.1.  A map is small at an eighth of the LDS: at a sixteenth the 32x32 net
+    // takes 80.5 ms, at a quarter the 24x24 net 5.2 for 4.6.)
     CnnSegPlan four;
     bool tail = fits(y.nb, true, 4, four) || (fits(y.nb, true, 1, g) && s0 + 1 >= y.nb);
     int s1 = s0;
@@ -673,6 +682,8 @@ void cnn_plan_segments(CnnLayout& y) {
         if (fits(e, false, 1, g)) s1 = e;
       if (s1 == s0) return;                                  // not even one stage
     }
+    // Up to eight images per group: 64 variants of an 8x8 net over 4,000 images
+    // 3.3 ms with four, 2.4 with eight (2.1 with sixteen); the 32x32 net 68.1 and 66.6.
     for (int G = 1; G <= 8; ++G) fits(s1, tail, G, g);
     ++n;
     if (tail) break;
@@ -730,9 +741,11 @@ gevo_status cnn_layout(const gevo_cnn_config* c, int64_t n_test, CnnLayout& y) {
   y.act_vs = act;
   cnn_plan_segments(y);
   if (y.nseg > 0) {
-    // Images per segment launch: the maps between segments about fill the
-    // 256 MB last-level cache, so what one segment writes the next one finds
-    // there; 4,096 at most, 64 at least.
+    // Images per segment launch: maps between segments of at most 256 MB, which
+    // is workspace; 4,096 images at most, 64 at least.  Larger launches leave fewer
+    // last rounds, smaller ones did not gain from the last-level cache: 64 variants
+    // of the 32x32 net 71.3, 68.4, 66.6, 65.6 and 65.3 ms with 64, 128, 256, 512 and
+    // 2,000 MB, 32 of a 32x32x4 net 7.4, 7.4, 7.4, 7.0 and 6.7.
     size_t most = (size_t)ch;
     for (int i = 0; i + 1 < y.nseg; ++i) {
       const int j = y.seg[i].s1 - 1;                  // the map it writes
@@ -910,6 +923,9 @@ gevo_status cnn_predict_segments(gevo_cnn* h) {
       a.G = g.G;
       a.groups = (images + g.G - 1) / g.G;
       // several groups per workgroup once every CU has eight workgroups to run
+      // (64 variants of the 32x32 net: 68.4, 67.9 and 72.0 ms with one, four and eight
+      // groups, 66.6 by this rule; 32 of a 32x32x4 net over 1,000 images: one as by
+      // this rule 7.4, four 11.7)
       a.per_wg = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)a.groups * y.P / (256 * 8)));
       a.n_test = img0 + images; a.img0 = img0;                 // the launch's images and no further
       a.lds = g.x + g.y;

@@ -87,7 +87,10 @@ template <int HP, int BP>
 struct Fused2Lds {
   static constexpr int NW = HP / 32;     // waves of a group
   // Two groups of waves where one would leave a SIMD with a single wave and
-  // a block is short: each takes every second column block (kloop_groups).
+  // a block is short: each takes every second column block (kloop_groups; both
+  // sides' times stand there).  At batch tile 64 one wave per SIMD stays: a block
+  // holds two row tiles, and the loop's staging, one 16-byte piece of X per
+  // thread, is laid out for one.  Two groups were not built for it.
   static constexpr int GROUPS = HP == 128 && BP == 32 ? 2 : 1;
   static constexpr int NT = 64 * NW * GROUPS;   // threads
   static constexpr int XS = 36;          // row pitch of that loop's X blocks: 32 rows' 8-byte reads touch every bank

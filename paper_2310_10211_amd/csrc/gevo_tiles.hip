@@ -882,6 +882,12 @@ hipError_t launch_tile_fwd(const TileFwdArgs<S>& a, int P, hipStream_t s, const 
   if (a.Kp % 32 || a.Np % 32 || a.R % 32 || a.Kp <= 0 || a.Np <= 0 || a.R <= 0) return hipErrorInvalidValue;
   // Rounds of 256 workgroups (one per CU) times the products of a wave, with
   // one product's worth for the operands that a smaller tile loads more often.
+  // ms per prediction by this rule, and with (2, 8), (2, 4), (1, 4), (1, 2) and (1, 1)
+  // for every launch: 64 variants of 784-256-10, 10,000 rows 2.09 (2.08, 2.11, 3.57,
+  // 4.08, 3.20); 4 of 784-128-10, 512 rows 0.035 (0.199, 0.111, 0.067, 0.045, 0.035); 128
+  // of 784-256-10, 250 rows 0.139 (0.223, 0.136, 0.198, 0.219, 0.188); 256 of 784-32-10,
+  // 2,048 rows 0.375 (1.49, 1.52, 0.38, 0.42, 0.37).  It is furthest off where two
+  // tiles cost nearly the same: 32 of 784-512-256-10, 3,000 rows 0.91 (0.95, 0.86, ...).
   const int64_t NB = a.Np / 32, NRT = a.R / 32;
   auto cost = [&](int nt, int rt) {
     const int64_t wg = (NB + 4 * nt - 1) / (4 * nt) * ((NRT + rt - 1) / rt) * P;
