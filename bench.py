@@ -34,7 +34,7 @@ KERNEL_SOURCES = ["gevo_device.h", "gevo_internal.h", "gevo_kernels.hip", "gevo_
                   "gevo_bwd.hip", "gevo_gemm.hip", "gevo_predict.hip"]
 # rocprofv3 kernel-name stem -> kernel kind of gevo_pop_kernel_stats (training kind, predict kind)
 KERNEL_KIND_OF = {"k_fused2": ("fused_train", None), "k_stream_layer": ("layer_train", "layer_fwd"),
-                  "k_layer": (None, "layer_fwd"), "k_out_fwd": ("out_train", None),
+                  "k_layer_train": ("layer_train", None), "k_layer": (None, "layer_fwd"), "k_out_fwd": ("out_train", None),
                   "k_out_upd": ("out_train", None), "k_out": (None, "out_predict"),
                   "k_bwd_gemm": ("bwd", None), "k_pred_gemm<true>": (None, "fwd_out"),
                   "k_pred_gemm<false>": (None, "layer_fwd"), "k_wt_bf16": (None, "weight_copy"),
