@@ -19,7 +19,7 @@
 // lane exchange), narrower ones give the halves different row ranges.
 // The layer-by-layer kernels moved every map through memory and re-read nine
 // neighbours per depthwise output from LDS: 139 ms for 64 variants of the
-// 32x32 net (stem 32, blocks 128 to 512) over 10,000 images, 68.3 ms here; 0.72
+// 32x32 net (stem 32, blocks 128 to 512) over 10,000 images, 66.2 ms here; 0.72
 // and 0.10 ms for 6 variants of an 8x8 net over 600 images.  Bound by vector
 // instructions: about 200 a lane for each 32 x 32 tile of a produced map
 // (rectify and round 24, depthwise 50 to 100, its output 40, addresses), at two

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import synthetic
+from conftest import training_path
 
 pytestmark = pytest.mark.gpu
 
@@ -62,20 +63,25 @@ def test_noalloc_prediction_equals_prediction_twice_second_smaller():
     pop.close()
 
 
-@pytest.mark.parametrize("i,dims,batch", [
-    (5, [1024, 256, 128, 10], 256),     # hidden layers on the prediction GEMM and the older forward kernel
-    (2, [784, 96, 10], 64),             # fp32
+@pytest.mark.parametrize("i,dims,batch,P,path", [
+    (5, [1024, 256, 128, 10], 256, 5, "tiles"),        # hidden layers on the prediction GEMM and the older forward kernel
+    (5, [1024, 256, 128, 10], 256, 33, "streamed 2"),  # masters brought up to date from the trained register images
+    (5, [1024, 256, 96, 10], 256, 65, "streamed 1"),
+    (3, [784, 256, 10], 128, 33, "fused"),
+    (2, [784, 96, 10], 64, 5, "tiles"),                # fp32
 ])
-def test_noalloc_prediction_other_paths(i, dims, batch):
+def test_noalloc_prediction_other_paths(i, dims, batch, P, path):
     _torch()
     import paper_2310_10211_amd as g
-    cfg = synthetic.config(i, P=5, dims=dims, batch=batch)
+    cfg = synthetic.config(i, P=P, dims=dims, batch=batch)
     data = _data(i, 500, 400, dims)
-    print(f"[gpu] noalloc paths: P=5 dims={dims}", flush=True)
+    print(f"[gpu] noalloc paths: P={P} dims={dims}", flush=True)
     pop = g.Population(cfg, data["x_train"], data["y_train"], data["x_test"], data["y_test"])
-    pop.train_epoch(0)
-    a, b = _both(pop)
-    _same(a, b, str(dims))
+    assert training_path(pop, lambda: pop.train_epoch(0)) == path
+    pop.predict_noalloc()                              # first, so that it reads what training left
+    b = pop.scores()
+    pop.predict()
+    _same(pop.scores(), b, str(dims))
     pop.close()
 
 
