@@ -333,17 +333,30 @@ __global__ __launch_bounds__(256, 2) void k_layer(LayerArgs<S> a) {
     }
   };
 
-  if (nblk == 1) fill(0);
-  for (int pass = 0; pass < npass; ++pass) {
-    const int row0 = pass * PASS;
-    const int ntiles = min(PASS, R - row0) / 32;
-    f32x16_t acc[2] = {zero16(), zero16()};
-    for (int blk = 0; blk < nblk; ++blk) {
-      if (nblk > 1) fill(blk);
-      forward(blk, row0, ntiles, acc);
-      if (nblk > 1) __syncthreads();
+  // One block has a loop of its own: the loop over blocks around it cost 512
+  // variants of 784-96-10 over 10,000 rows 3.59 ms for 3.16, 256 of 784-300-10 over
+  // 3,000 rows 1.59 for 1.45.
+  if (nblk == 1) {
+    fill(0);
+    for (int pass = 0; pass < npass; ++pass) {
+      const int row0 = pass * PASS;
+      const int ntiles = min(PASS, R - row0) / 32;
+      f32x16_t acc[2] = {zero16(), zero16()};
+      forward(0, row0, ntiles, acc);
+      epilogue(row0, ntiles, acc);
     }
-    epilogue(row0, ntiles, acc);
+  } else {
+    for (int pass = 0; pass < npass; ++pass) {
+      const int row0 = pass * PASS;
+      const int ntiles = min(PASS, R - row0) / 32;
+      f32x16_t acc[2] = {zero16(), zero16()};
+      for (int blk = 0; blk < nblk; ++blk) {
+        fill(blk);
+        forward(blk, row0, ntiles, acc);
+        __syncthreads();
+      }
+      epilogue(row0, ntiles, acc);
+    }
   }
   vt_add(a.vtime, v, vt0);
 }
